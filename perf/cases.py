@@ -192,6 +192,12 @@ def _lse(q, k, c):
     return out
 
 
+def _kcap(c, roles):
+    """Quotas, and rows for any labels: the budget, rounded up per bucket."""
+    quota, _, kcap = kve.role_allocate(roles, R, ALPHA, c["budget"], c["W"])
+    return quota, max(kcap, math.ceil(c["budget"] * c["N"]) + R)
+
+
 def prepare(case, seed):
     c = dict(case)
     op, L, B, Hq, Hkv, N, W, d = (c[x] for x in ("op", "L", "B", "Hq", "Hkv", "N", "W", "d"))
@@ -203,7 +209,7 @@ def prepare(case, seed):
     if op == "evict":
         s["v"] = _normal((L, B, Hkv, N, d), c, _gen(seed + 1))
         s["roles"], s["roles_dev"] = roles, torch.from_numpy(roles).to(DEV)
-        kcap = kve.role_allocate(roles, R, ALPHA, c["budget"], W)[2]
+        kcap = _kcap(c, roles)[1]
         s["bufs"] = pipeline.alloc_buffers(s["k"], Hq, W, R, kcap)
         s["q1"] = _normal((L, B, Hq, d), c, _gen(seed + 2))
         s["out"] = torch.empty((L, B, Hq, d), dtype=torch.float32, device=DEV)
@@ -219,7 +225,7 @@ def prepare(case, seed):
     elif op == "topk":
         s["score"] = _pooled_scores(c, seed, roles)
         s["roles_dev"] = torch.from_numpy(roles).to(DEV)
-        quota, _, s["kcap"] = kve.role_allocate(roles, R, ALPHA, c["budget"], W)
+        quota, s["kcap"] = _kcap(c, roles)
         s["quota"] = torch.from_numpy(quota).to(DEV)
         s["idx"] = torch.full((L, B, Hkv, s["kcap"]), -1, dtype=torch.int32, device=DEV)
         s["count"] = torch.zeros((L, B, Hkv), dtype=torch.int32, device=DEV)
