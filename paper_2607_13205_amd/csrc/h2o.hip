@@ -4,29 +4,30 @@
 // softmax weight p_i(t), kept per (layer, head); here summed over the G query
 // heads of each KV head.
 //
-// Both passes are the causal QK^T on the matrix cores (bf16 32x32x16, fp32
-// 32x32x2) with operands streamed through a two-slot LDS ring by
-// direct-to-LDS loads, as in the SnapKV kernels:
-//   h2o_pass1  one workgroup per (KV group, block of positions): its 128 rows
-//              are the G heads of the group at 128/G consecutive positions
+// Both passes are the causal QK^T on the matrix cores with operands streamed
+// through LDS by direct-to-LDS loads, as in the SnapKV kernels.  bf16
+// (h2o_pass1_x2, h2o_pass2_x2) multiplies 32x32x16 tiles from a two-slot ring;
+// float32 (h2o_pass1_f32, h2o_pass2_f32) splits its rows into float16 pairs.
+//   pass 1     one workgroup per (KV group, block of positions): its 256 rows
+//              are the G heads of the group at 256/G consecutive positions
 //              (position-major), query fragments in registers; the keys up to
 //              the block's last position stream through LDS and each lane
-//              keeps one row's running softmax denominator.  Writes
-//              -lse2/sl2 per row, the start value pass 2 needs, into rows of
-//              pitch NP = N rounded up to 64 floats per head.
-//   h2o_pass2  one workgroup per (query head, 128-key block), key blocks near
-//              0 (the most rows) first: four waves own 32 keys each (key
+//              keeps one row's running softmax denominator.  Writes the start
+//              value pass 2 needs (bf16: -lse2/sl2, float32: -lse2) per row,
+//              into rows of pitch NP = N rounded up to 64 floats per head.
+//   pass 2     one workgroup per (query head, 256-key block), key blocks near
+//              0 (the most rows) first: four waves own 64 keys each (key
 //              fragments in registers); every later query row of the head
-//              streams through LDS in 64-row chunks together with its
-//              -lse2/sl2, which starts the products, so that sl2 * acc =
-//              x - lse2 and each lane sums exp2 over its key's column
-//              directly.  One column sum per (query head, key).
+//              streams through LDS in 64-row chunks together with its start
+//              value, so that each lane sums exp2(x - lse2) over its keys'
+//              columns directly.  One column sum per (query head, key).
 //   h2o_heads  adds the G heads of each KV group, in head order.
 // Logits are in log2 units, x = scale * log2(e) * <q, k>.
 #include <algorithm>
 
 #include "kve_device.h"
 #include "kve_internal.h"
+#include "kve_split.h"
 #include "kve_stream.h"
 
 namespace kve {
@@ -203,143 +204,231 @@ __global__ __launch_bounds__(kThreads, 2) void h2o_pass1_x2(RowView qv, RowView 
     }
 }
 
-template <typename T, int D>
-__global__ __launch_bounds__(kThreads, 2) void h2o_pass1(RowView qv, RowView kv, int B, int Hq, int Hkv, int N,
-                                                         int NP, int npos, int nblk, float sl2,
-                                                         float* __restrict__ linit) {
-    using G = Geo<T, D>;
-    __shared__ __align__(16) char ring[kRing * G::C::BYTES];
+// float32 passes: the rows split into float16 pairs (kve_split.h), three
+// 16-bit products per float32 one, in the tiling of the bf16 passes: 256
+// register rows per workgroup as two sets of 32 per wave (128 registers of
+// fragments), 64-row chunks streamed.  A chunk lands in LDS as float32, each
+// wave splits a quarter of it into the two planes the products read, and the
+// next chunk's loads go out into the raw slot as soon as every wave has read
+// it: a chunk is split once per workgroup, about 450 vector cycles per wave
+// beside 3072 of products.  64.5 KB of LDS: two workgroups per CU.  Bound by the
+// products and the exponentials, like the bf16 passes: 32 query heads, N =
+// 16003, d = 128 take 5.99 ms (1.05 PFLOP/s of 16-bit products) against 15.45
+// ms with v_mfma_f32_32x32x2_f32 (0.14 PFLOP/s, 87% of that instruction's
+// rate); the scores are 2.9e-7 off their 64-bit values with either.
+template <int D>
+struct SplitLds {
+    using S = SplitChunk<D>;
+    __align__(16) char raw[S::Raw::BYTES];
+    __align__(16) char hi[S::PLANE];
+    __align__(16) char lo[S::PLANE];
+    __align__(16) float unscale[kKeys];
+};
+
+// acc (scaled products) times the scales of its chunk row and register row
+template <int RS>
+__device__ __forceinline__ void unscale_acc(f32x16 (&acc)[RS][2], const float* unscale, const float (&ls)[RS],
+                                            int lane) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        __builtin_amdgcn_sched_barrier(0);  // one block's scales in registers at a time
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+            const float4 v = *reinterpret_cast<const float4*>(unscale + 32 * b + c_row(4 * a, lane));
+            const float u[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int rs = 0; rs < RS; ++rs)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[rs][b][4 * a + e] *= u[e] * ls[rs];
+        }
+    }
+}
+
+template <int D>
+__global__ __launch_bounds__(kThreads, 2) void h2o_pass1_f32(RowView qv, RowView kv, int B, int Hq, int Hkv, int N,
+                                                             int NP, int npos, int nblk, float sl2,
+                                                             float* __restrict__ linit) {
+    using S = SplitChunk<D>;
+    __shared__ SplitLds<D> sh;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int Gh = Hq / Hkv;
-    // the KV head varies fastest: workgroups are dealt to the XCDs in turn, so
-    // (with Hkv a divisor or multiple of their number) each XCD keeps to a few
-    // heads and their key rows, re-read by every later position block, stay in
-    // its L2; within a head the longest causal rows come first
+    // block order as in h2o_pass1_x2
     int bid = blockIdx.x;
     const int j = bid % Hkv;
     bid /= Hkv;
     const int pb = nblk - 1 - bid % nblk;
     const int lb = bid / nblk;
     const int p0 = pb * npos;
-    // this lane's row: head g of the group at position pos (position-major)
-    const int r = wave * 32 + (lane & 31);
-    const int g = r % Gh;
-    const int pos = p0 + r / Gh;
-    const bool valid = r < npos * Gh && pos < N;
-    const size_t head = (size_t)lb * Hq + (size_t)j * Gh + g;
-
-    typename G::Frags qf;
-    load_row_frags<T, D>(qf, head_rows(qv, lb, B, j * Gh + g) + (long long)(valid ? pos : 0) * qv.s_token, valid,
-                         lane);
+    int lim[2];  // last key the row sees (-1: no row)
+    typename S::Frags qf[2];
+    float ls[2];  // scale of this lane's rows, times sl2
+#pragma unroll
+    for (int rs = 0; rs < 2; ++rs) {
+        const int r = wave * 64 + rs * 32 + (lane & 31);
+        const int pos = p0 + r / Gh;
+        const bool valid = r < npos * Gh && pos < N;
+        ls[rs] = sl2 * S::load_row(qf[rs],
+                                   head_rows(qv, lb, B, j * Gh + r % Gh) + (long long)(valid ? pos : 0) * qv.s_token,
+                                   valid, lane);
+        lim[rs] = valid ? pos : -1;
+    }
     const int t_end = min(N, p0 + npos);  // keys up to the block's last position
     const int nch = (t_end + kKeys - 1) / kKeys;
-    typename G::Rd rd;
-    rd.init(lane, 0);
-    typename G::Ring ring_io;
-    ring_io.open(nch, wave, lane, (unsigned)kv.s_token);
-    const RowChunks<T, D> src{head_rows(kv, lb, B, j), kv.s_token, 0, t_end};
-    ring_io.prologue(ring, src);
+    typename Geo<float, D>::Wr wr;
+    wr.init(wave, lane, (unsigned)kv.s_token);
+    const char* kbase = head_rows(kv, lb, B, j);
+    auto issue = [&](int c) { wr.issue(sh.raw, kbase + (long long)(c * kKeys) * kv.s_token, t_end - c * kKeys); };
+    issue(0);
 
-    const int lim = valid ? pos : -1;  // last key the row sees
-    RowSum rs;
-    for (int s0 = 0; s0 < nch; s0 += kRing) {
+    RowSum rsum[2];
+    auto logits = [&](f32x16 (&acc)[2][2], int s) {
+        S::template mma<true, 2>(acc, sh.hi, sh.lo, qf, lane);
+        unscale_acc<2>(acc, sh.unscale, ls, lane);
+        if ((s + 1) * kKeys > p0) {  // a key of the chunk lies after some row of the block
 #pragma unroll
-        for (int u = 0; u < kRing; ++u) {
-            const int s = s0 + u;
-            if (s >= nch) break;
-            ring_io.advance(ring, s, u, src);
-            f32x16 acc[2];
-            chunk_mma<T, D, kKeys, true>(acc, rd, ring + u * G::C::BYTES, qf, nullptr, lane);
-            if ((s + 1) * kKeys > p0) {  // a key of the chunk lies after some row of the block
+            for (int rs = 0; rs < 2; ++rs) {
                 // key of element (kb, i) = base + 32 kb + 8 (i / 4) + i % 4
-                const int last = lim - (s * kKeys + 4 * (lane >> 5));
+                const int last = lim[rs] - (s * kKeys + 4 * (lane >> 5));
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                     for (int i = 0; i < 16; ++i)
-                        if (32 * kb + 8 * (i >> 2) + (i & 3) > last) acc[kb][i] = -INFINITY;
+                        acc[rs][kb][i] = mask_neg(acc[rs][kb][i], last - (32 * kb + 8 * (i >> 2) + (i & 3)));
             }
-            rs.add(acc, sl2);
+        }
+    };
+#pragma unroll 1
+    for (int s = 0; s < nch; ++s) {
+        wait_vmcnt<0>();
+        lds_barrier();  // chunk s landed; every wave is done with the planes of chunk s - 1
+        S::convert(sh.raw, sh.hi, sh.lo, sh.unscale, wave, lane);
+        lds_barrier();  // planes written, raw slot read
+        if (s + 1 < nch) issue(s + 1);
+        // a second round, of the whole wave, when a sum left [0, 2^64]: the
+        // exponentials replaced the logits, and the planes stay until the next
+        // barrier
+        float ln[2];
+#pragma unroll 1
+        for (bool again = false;; again = true) {
+            f32x16 acc[2][2];
+            logits(acc, s);
+            if (again) {
+                row_sums_fix<2>(rsum, acc, 1.0f, ln);
+                break;
+            }
+            if (row_sums_try<2>(rsum, acc, 1.0f, ln)) break;
         }
     }
-    // the two lane halves hold the same row and different keys
-    lse2_merge(rs.m, rs.l, __shfl_xor(rs.m, 32), __shfl_xor(rs.l, 32));
-    if (lane < 32 && valid) linit[head * NP + pos] = -rs.lse2() / sl2;
+#pragma unroll
+    for (int rs = 0; rs < 2; ++rs) {
+        // the two lane halves hold the same row and different keys
+        lse2_merge(rsum[rs].m, rsum[rs].l, __shfl_xor(rsum[rs].m, 32), __shfl_xor(rsum[rs].l, 32));
+        const int g = S::opaque(wave * 64 + rs * 32 + (lane & 31)) % Gh;
+        if (lane < 32 && lim[rs] >= 0)
+            linit[((size_t)lb * Hq + (size_t)j * Gh + g) * NP + lim[rs]] = -rsum[rs].lse2();
+    }
 }
 
-template <typename T, int D>
-__global__ __launch_bounds__(kThreads, 2) void h2o_pass2(RowView qv, RowView kv, int B,
-                                                         const float* __restrict__ linit, int heads, int Hq,
-                                                         int Hkv, int N, int NP, float sl2,
-                                                         float* __restrict__ colsum) {
-    using G = Geo<T, D>;
-    __shared__ __align__(16) char ring[kRing * G::C::BYTES];
-    __shared__ __align__(16) float sli[kRing][kKeys];  // -lse2/sl2 of each chunk row
+// linit: -lse2 of every row (log2 units)
+template <int D>
+__global__ __launch_bounds__(kThreads, 2) void h2o_pass2_f32(RowView qv, RowView kv, int B,
+                                                             const float* __restrict__ linit, int heads, int Hq,
+                                                             int Hkv, int N, int NP, float sl2,
+                                                             float* __restrict__ colsum) {
+    using S = SplitChunk<D>;
+    constexpr int kBlock = 2 * kKeyBlock;
+    __shared__ SplitLds<D> sh;
+    __shared__ __align__(16) float sli[2][kKeys];  // -lse2 of each chunk row
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int Gh = Hq / Hkv;
     const int kb = blockIdx.x / heads;  // key blocks near 0 (the most rows) first
     const size_t head = (size_t)(blockIdx.x - kb * heads);  // over all layers and samples
     const size_t lbj = head / Gh;                            // (layer, sample, KV head)
-    const int kb0 = kb * kKeyBlock;
-    const int key = kb0 + wave * 32 + (lane & 31);
-
-    typename G::Frags kf;
+    const int kb0 = kb * kBlock;
+    int key[2];
+    typename S::Frags kf[2];
+    float ls[2];  // scale of this lane's keys, times sl2
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+        key[ks] = kb0 + wave * 64 + ks * 32 + (lane & 31);
+        ls[ks] = sl2 * S::load_row(kf[ks],
+                                   head_rows(kv, (int)(lbj / Hkv), B, (int)(lbj % Hkv)) +
+                                       (long long)(key[ks] < N ? key[ks] : 0) * kv.s_token,
+                                   key[ks] < N, lane);
+    }
     const char* qhead = head_rows(qv, (int)(head / Hq), B, (int)(head % Hq));
-    load_row_frags<T, D>(kf, head_rows(kv, (int)(lbj / Hkv), B, (int)(lbj % Hkv)) + (long long)(key < N ? key : 0) * kv.s_token,
-                         key < N, lane);
     // rows kb0 .. N - 1 of this head
     const int nch = (N - kb0 + kKeys - 1) / kKeys;
-    typename G::Rd rd;
-    rd.init(lane, 0);
-    typename G::Wr wr;
+    typename Geo<float, D>::Wr wr;
     wr.init(wave, lane, (unsigned)qv.s_token);
     // chunk c: rows from kb0 + 64 c, with their 64 start values (256 bytes:
     // four 16-byte pieces per wave, lanes 0..3).  r0 is a multiple of 64 below
     // N, so the 64 values lie inside the head's row of pitch NP and start
     // 256-byte aligned; rows past N are masked.
-    auto issue = [&](int c, int slot) {
+    auto issue = [&](int c) {
         const int r0 = kb0 + c * kKeys;
-        const char* rows = qhead + (long long)r0 * qv.s_token;
-        wr.issue(ring + slot * G::C::BYTES, rows, N - r0);
+        wr.issue(sh.raw, qhead + (long long)r0 * qv.s_token, N - r0);
         if (lane < 4)
             lds_dma16(reinterpret_cast<const char*>(linit + head * NP + r0), (unsigned)(wave * 64 + lane * 16),
-                      reinterpret_cast<const char*>(&sli[slot][wave * 16]));
+                      reinterpret_cast<const char*>(&sli[c & 1][wave * 16]));
     };
-    for (int c = 0; c < min(kRing - 1, nch); ++c) issue(c, c);
+    issue(0);
 
-    float col = 0.0f;
-    for (int s0 = 0; s0 < nch; s0 += kRing) {
+    float col[2] = {0.0f, 0.0f};
+#pragma unroll 1
+    for (int s = 0; s < nch; ++s) {
+        wait_vmcnt<0>();
+        lds_barrier();  // chunk s landed; every wave is done with the planes of chunk s - 1
+        S::convert(sh.raw, sh.hi, sh.lo, sh.unscale, wave, lane);
+        lds_barrier();  // planes written, raw slot read
+        if (s + 1 < nch) issue(s + 1);
+        f32x16 acc[2][2];
+        S::template mma<true, 2>(acc, sh.hi, sh.lo, kf, lane);
+        // x - lse2 = acc * scales + linit of the row
 #pragma unroll
-        for (int u = 0; u < kRing; ++u) {
-            const int s = s0 + u;
-            if (s >= nch) break;
-            wait_chunk<G::Wr::LPW + 1, kRing - 2>(min(kRing - 2, nch - 1 - s));
-            lds_barrier();
-            if (s + kRing - 1 < nch) issue(s + kRing - 1, (u + kRing - 1) % kRing);
-            f32x16 acc[2];
-            chunk_mma<T, D, kKeys, true>(acc, rd, ring + u * G::C::BYTES, kf, &sli[u][0], lane);
-            const int r0 = kb0 + s * kKeys;
-            if (r0 < kb0 + kKeyBlock || r0 + kKeys > N) {  // rows before some key, or past N
+        for (int b = 0; b < 2; ++b) {
+            __builtin_amdgcn_sched_barrier(0);  // one block's scales and start values in registers at a time
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                const int o = 32 * b + c_row(4 * a, lane);
+                const float4 v = *reinterpret_cast<const float4*>(sh.unscale + o);
+                const float4 w = *reinterpret_cast<const float4*>(&sli[s & 1][o]);
+                const float u[4] = {v.x, v.y, v.z, v.w}, c[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        acc[ks][b][4 * a + e] = fmaf(acc[ks][b][4 * a + e], u[e] * ls[ks], c[e]);
+            }
+        }
+        const int r0 = kb0 + s * kKeys;
+        if (r0 < kb0 + kBlock || r0 + kKeys > N) {  // rows before some key, or past N
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
                 // row of element (b, i) = r0 + 32 b + 8 (i / 4) + 4 (lane / 32) + i % 4; it
                 // counts iff key <= row < N
-                const int lo = key - (r0 + 4 * (lane >> 5));
+                const int lo = key[ks] - (r0 + 4 * (lane >> 5));
                 const int hi = N - (r0 + 4 * (lane >> 5));
 #pragma unroll
                 for (int b = 0; b < 2; ++b)
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
                         const int off = 32 * b + 8 * (i >> 2) + (i & 3);
-                        if (off < lo || off >= hi) acc[b][i] = -INFINITY;
+                        acc[ks][b][i] = mask_neg(acc[ks][b][i], (off - lo) | (hi - 1 - off));
                     }
             }
-            col += exp2_sum(acc, sl2);
         }
+        col[0] += exp2_sum(acc[0], 1.0f);
+        col[1] += exp2_sum(acc[1], 1.0f);
     }
-    // the two lane halves hold the same key and different rows
-    col += __shfl_xor(col, 32);
-    if (lane < 32 && key < N) colsum[head * N + key] = col;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+        // the two lane halves hold the same key and different rows
+        const float c = col[ks] + __shfl_xor(col[ks], 32);
+        if (lane < 32 && key[ks] < N) colsum[head * N + key[ks]] = c;
+    }
 }
 
 // Pass 2 with two register key sets per wave (bf16): 256 keys per workgroup,
@@ -378,8 +467,8 @@ __global__ __launch_bounds__(kThreads, 2) void h2o_pass2_x2(RowView qv, RowView 
     rd.init(lane, 0);
     typename G::Wr wr;
     wr.init(wave, lane, (unsigned)qv.s_token);
-    // chunk c: rows from kb0 + 64 c, with their 64 start values (256 bytes:
-    // four 16-byte pieces per wave, lanes 0..3); as in h2o_pass2
+    // chunk c: rows from kb0 + 64 c, with their 64 start values, as in
+    // h2o_pass2_f32
     auto issue = [&](int c, int slot) {
         const int r0 = kb0 + c * kKeys;
         const char* rows = qhead + (long long)r0 * qv.s_token;
@@ -451,23 +540,21 @@ hipError_t run_h2o(const RowView& qv, const RowView& kv, int L, int B, int Hq, i
     const int Gh = Hq / Hkv;
     const int NP = h2o_pitch(N);
     const int heads = L * B * Hq;
-    // bf16: two register row sets per wave (fp32 fragments are twice the
-    // registers and keep one)
-    constexpr bool kX2 = sizeof(T) == 2;
-    const int npos = (kX2 ? 2 : 1) * kH2oRowsPerGroup / Gh;  // positions per pass-1 workgroup
+    constexpr int kRows = 2 * kH2oRowsPerGroup;  // two register row sets per wave
+    const int npos = kRows / Gh;                 // positions per pass-1 workgroup
     const int nblk = (N + npos - 1) / npos;
-    const int kblock = (kX2 ? 2 : 1) * kKeyBlock;
-    const int nkb = (N + kblock - 1) / kblock;
-    if constexpr (kX2) {
-        hipLaunchKernelGGL((h2o_pass1_x2<T, D>), dim3((unsigned)((size_t)L * B * Hkv * nblk)), dim3(kThreads), 0,
-                           st, qv, kv, B, Hq, Hkv, N, NP, npos, nblk, sl2, linit);
-        hipLaunchKernelGGL((h2o_pass2_x2<T, D>), dim3((unsigned)((size_t)heads * nkb)), dim3(kThreads), 0, st, qv,
-                           kv, B, linit, heads, Hq, Hkv, N, NP, sl2, colsum);
+    const int nkb = (N + 2 * kKeyBlock - 1) / (2 * kKeyBlock);
+    const dim3 grid1((unsigned)((size_t)L * B * Hkv * nblk)), grid2((unsigned)((size_t)heads * nkb));
+    if constexpr (sizeof(T) == 2) {
+        hipLaunchKernelGGL((h2o_pass1_x2<T, D>), grid1, dim3(kThreads), 0, st, qv, kv, B, Hq, Hkv, N, NP, npos, nblk,
+                           sl2, linit);
+        hipLaunchKernelGGL((h2o_pass2_x2<T, D>), grid2, dim3(kThreads), 0, st, qv, kv, B, linit, heads, Hq, Hkv, N,
+                           NP, sl2, colsum);
     } else {
-        hipLaunchKernelGGL((h2o_pass1<T, D>), dim3((unsigned)((size_t)L * B * Hkv * nblk)), dim3(kThreads), 0, st,
-                           qv, kv, B, Hq, Hkv, N, NP, npos, nblk, sl2, linit);
-        hipLaunchKernelGGL((h2o_pass2<T, D>), dim3((unsigned)((size_t)heads * nkb)), dim3(kThreads), 0, st, qv,
-                           kv, B, linit, heads, Hq, Hkv, N, NP, sl2, colsum);
+        hipLaunchKernelGGL((h2o_pass1_f32<D>), grid1, dim3(kThreads), 0, st, qv, kv, B, Hq, Hkv, N, NP, npos, nblk,
+                           sl2, linit);
+        hipLaunchKernelGGL((h2o_pass2_f32<D>), grid2, dim3(kThreads), 0, st, qv, kv, B, linit, heads, Hq, Hkv, N, NP,
+                           sl2, colsum);
     }
     const size_t total = (size_t)L * B * Hkv * N;
     hipLaunchKernelGGL(h2o_heads, dim3((unsigned)std::min<size_t>((total + kThreads - 1) / kThreads, 4096)),

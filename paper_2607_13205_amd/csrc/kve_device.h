@@ -105,6 +105,13 @@ __device__ __forceinline__ int c_row(int i, int lane) {
     return 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
 }
 
+// x, or -inf where `left` is negative: a bit select on the sign, which needs
+// no compare mask in scalar registers per element.
+__device__ __forceinline__ float mask_neg(float x, int left) {
+    const uint32_t m = (uint32_t)(left >> 31);
+    return __uint_as_float((__float_as_uint(x) & ~m) | (0xff800000u & m));
+}
+
 // Merge two (max, sum-of-exp2) pairs of the same row.  -inf max means empty.
 __device__ __forceinline__ void lse2_merge(float& m, float& l, float mo, float lo) {
     const float mn = fmaxf(m, mo);

@@ -10,10 +10,10 @@
 namespace kve {
 
 // ---------------------------------------------------------------------------
-// H2O score: pass 1 one start value (-lse2 / sl2) per (layer, sample, query
+// H2O score: pass 1 one start value per (layer, sample, query
 // head, row), in rows of pitch h2o_pitch(N) floats; pass 2 one column sum per
-// (query head, key), added over the group's heads by a last step.  A pass-1 workgroup covers kH2oRowsPerGroup rows:
-// the G heads of a KV group at kH2oRowsPerGroup / G positions.
+// (query head, key), added over the group's heads by a last step.  A pass-1 workgroup covers 2 kH2oRowsPerGroup
+// rows: the G heads of a KV group at 2 kH2oRowsPerGroup / G positions.
 // ---------------------------------------------------------------------------
 constexpr int kH2oRowsPerGroup = 128;
 

@@ -46,15 +46,19 @@ __device__ __forceinline__ int chunk_swz(int r, int c) {
 // its lines are the first the caches give up.
 template <bool NT = false>
 __device__ __forceinline__ void lds_dma16(const char* base, unsigned voff, const char* lds_dst) {
-    const unsigned m0 = __builtin_amdgcn_readfirstlane(
-        (unsigned)(size_t)(const __attribute__((address_space(3))) char*)lds_dst);
+    // a generic pointer into LDS holds the LDS address in its low 32 bits (a
+    // cast to an LDS pointer would add a null test per load)
+    const unsigned m0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)lds_dst);
     // the LDS base goes in M0; one wait state must separate its write from the
-    // direct-to-LDS load that reads it
+    // direct-to-LDS load that reads it, and five a vector instruction that
+    // writes the base's scalar registers (a scalar register restored from a
+    // spill comes back by v_readlane) from the load: the compiler counts no wait
+    // states for an instruction inside inline assembly
     if constexpr (NT)
-        asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
+        asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1 nt"
                      :: "v"(voff), "s"(base), "{m0}"(m0) : "memory");
     else
-        asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+        asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1"
                      :: "v"(voff), "s"(base), "{m0}"(m0) : "memory");
 }
 
@@ -108,12 +112,13 @@ struct ChunkWriter {
     using C = KChunk<T, D, KEYS>;
     static constexpr int LPW = C::BYTES / (NWAVES * 1024);
     static_assert(C::BYTES % (NWAVES * 1024) == 0, "chunk must split into whole 1 KiB wave loads");
-    // chunk rows between a lane's consecutive loads; when they span whole
-    // swizzle periods (16 rows) all loads of a lane share its column, so one
-    // offset serves them all and the wave-uniform base steps by RJ rows
+    // chunk rows between a lane's consecutive loads; the swizzle repeats every
+    // 16 rows, so NOFF offsets serve all loads of a lane and the wave-uniform
+    // base steps by whole periods
     static constexpr int RJ = NWAVES * 1024 / C::ROW;
-    static constexpr bool kOneOff = RJ % 16 == 0;
-    unsigned goff[kOneOff ? 1 : LPW];
+    static constexpr int NOFF = RJ % 16 == 0 ? 1 : 16 / RJ;
+    static_assert(RJ % 16 == 0 || 16 % RJ == 0, "loads step by a fraction or a multiple of the swizzle period");
+    unsigned goff[NOFF];
     unsigned rstride;
     int wv, lane;
 
@@ -122,35 +127,31 @@ struct ChunkWriter {
         lane = lane_;
         rstride = row_stride;
 #pragma unroll
-        for (int j = 0; j < (kOneOff ? 1 : LPW); ++j) {
-            const int r = row_of(j);
-            const int o = (j * NWAVES + wv) * 1024 + lane * 16;
-            const int c = ((o - r * C::ROW) >> 4) ^ chunk_swz_bits<C::ROW>(r);  // inverse of chunk_swz
-            goff[j] = (unsigned)r * row_stride + (unsigned)(c * 16);
-        }
+        for (int j = 0; j < NOFF; ++j) goff[j] = (unsigned)row_of(j) * row_stride + piece_of(j);
     }
-    // chunk row of this lane's load j
+    // chunk row of this lane's load j, and the byte of that row it takes
     __device__ __forceinline__ int row_of(int j) const { return ((j * NWAVES + wv) * 1024 + lane * 16) / C::ROW; }
-    // byte offset of this lane's load j from the chunk's first row
-    __device__ __forceinline__ unsigned off_of(int j) const {
-        return kOneOff ? goff[0] + (unsigned)(j * RJ) * rstride : goff[j];
+    __device__ __forceinline__ unsigned piece_of(int j) const {
+        const int r = row_of(j);
+        const int o = (j * NWAVES + wv) * 1024 + lane * 16;
+        return (unsigned)((((o - r * C::ROW) >> 4) ^ chunk_swz_bits<C::ROW>(r)) << 4);  // inverse of chunk_swz
     }
     // rows: first key row of the chunk (wave-uniform); valid: rows in bounds
     __device__ __forceinline__ void issue(char* slot, const char* rows, int valid) const {
         if (valid >= KEYS) {
 #pragma unroll
-            for (int j = 0; j < LPW; ++j) {
-                if constexpr (kOneOff)
-                    lds_dma16<NT>(rows + (size_t)(j * RJ) * rstride, goff[0], slot + (j * NWAVES + wv) * 1024);
-                else
-                    lds_dma16<NT>(rows, goff[j], slot + (j * NWAVES + wv) * 1024);
-            }
+            for (int j = 0; j < LPW; ++j)
+                lds_dma16<NT>(rows + (size_t)(j / NOFF * NOFF * RJ) * rstride, goff[j % NOFF],
+                              slot + (j * NWAVES + wv) * 1024);
         } else {
 #pragma unroll
             for (int j = 0; j < LPW; ++j) {
-                const int r = row_of(j);
-                const unsigned o = off_of(j);
-                lds_dma16<NT>(rows, r < valid ? o : o - (unsigned)r * rstride, slot + (j * NWAVES + wv) * 1024);
+                // worked out here (rare), not held in registers across the loop
+                int ln = lane;
+                asm volatile("" : "+v"(ln));
+                const int o = (j * NWAVES + wv) * 1024 + ln * 16, r = o / C::ROW;
+                const unsigned p = (unsigned)((((o - r * C::ROW) >> 4) ^ chunk_swz_bits<C::ROW>(r)) << 4);
+                lds_dma16<NT>(rows, r < valid ? (unsigned)r * rstride + p : p, slot + (j * NWAVES + wv) * 1024);
             }
         }
     }

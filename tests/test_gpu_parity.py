@@ -259,6 +259,48 @@ def test_h2o_score_logit_spikes_match_oracle(K, wl):
     check_scores(f64(score), ref, wl.name)
 
 
+def _f32_logit_bound(q, k, Hkv, scale, lo_terms=3):
+    """Largest error of a float32 logit taken as float16 pairs, and twice that
+    for a probability (its logit and its row's log-sum-exp): per product the
+    roundings of the two splits and the term left out (2^-24 each), and the
+    sums' 24 roundings per 128 elements, against sum |q| |k|."""
+    G = q.shape[2] // Hkv
+    mass = np.matmul(np.abs(f64(q)), np.abs(np.repeat(f64(k), G, axis=2)).swapaxes(-1, -2)).max()
+    return 2 * (lo_terms + 24) * 2.0 ** -24 * scale * mass
+
+
+@pytest.mark.parametrize("N,Hq,Hkv,d", [(1, 1, 1, 64), (63, 2, 2, 128), (64, 4, 1, 128), (65, 3, 1, 64),
+                                        (257, 2, 1, 128), (300, 8, 1, 64), (530, 6, 2, 128)])
+@pytest.mark.parametrize("kind", ["plain", "magnitudes", "minus_inf"])
+def test_h2o_f32_split_matches_float64(K, N, Hq, Hkv, d, kind):
+    """The float32 passes (rows as float16 pairs with a power of two per row)
+    against the 64-bit scores, at the edges of the 64-row chunks and 256-row
+    blocks: rows of ordinary size; rows of very different sizes, whose logits
+    are ordinary; keys with one -inf element, which draw no mass."""
+    note(f"h2o f32 split N={N} Hq={Hq} Hkv={Hkv} d={d} {kind}")
+    g = torch.Generator().manual_seed(N + d)
+    q = torch.randn((1, 1, Hq, N, d), generator=g)
+    k = torch.randn((1, 1, Hkv, N, d), generator=g)
+    if kind == "magnitudes":
+        # one row size per head pair: products keep their size, elements span 2^-100 .. 2^100
+        e = torch.randint(-100, 101, (1, 1, Hkv, 1, 1), generator=g).double()
+        k = (k.double() * 2.0 ** e).float()
+        q = (q.double() * 2.0 ** -e.repeat_interleave(Hq // Hkv, dim=2)).float()
+        k[:, :, :, 1::5] *= 2.0 ** -20
+    if kind == "minus_inf":
+        q[..., 3] = q[..., 3].abs() + 0.1
+        k[:, :, :, 1::7, 3] = -math.inf
+    score = K.h2o_score(q.cuda(), k.cuda())
+    torch.cuda.synchronize()
+    ref = O.h2o_score(f64(q), f64(k), Hkv)
+    kf = torch.where(torch.isinf(k), torch.zeros(()), k)
+    tol = _f32_logit_bound(q, kf, Hkv, d ** -0.5) + 2e-6  # the exponentials and the sums of probabilities
+    got = f64(score)
+    assert np.all(np.isfinite(got))
+    err = np.abs(got - ref)
+    assert np.all(err <= tol * np.abs(ref) + 1e-30), float((err / (np.abs(ref) + 1e-30)).max())
+
+
 def _token_major(x, pad):
     """x [L, B, H, T, d] as a view of a token-major tensor [L, B, T, H, d + pad]
     (NaN in the padding, which must never be read)."""
