@@ -412,6 +412,42 @@ def test_topk_many_segments_take_the_four_wave_workgroups(K, R, N):
     _topk_check(K, score, roles, quota, W, R)
 
 
+# (segments as L, B, Hkv), N, R: the whole-segment kernel at the edges of its
+# forms (4, 8 and 16 keys per thread), the split kernels (two slices up to 15,
+# ragged last ones, eight buckets), the general kernel where a segment is too
+# short to split, where segments are many (16-wave and 4-wave workgroups)
+TOPK_ROUTES = [((1, 1, 2), 1025, 4), ((1, 1, 2), 4096, 2), ((1, 1, 2), 4097, 8), ((1, 2, 1), 8193, 4),
+               ((1, 1, 2), 16384, 4), ((1, 1, 2), 16385, 4), ((1, 1, 1), 16385, 8), ((1, 2, 1), 33025, 8),
+               ((1, 1, 2), 70001, 4), ((1, 1, 1), 131071, 1), ((1, 1, 65), 16385, 4), ((4, 2, 64), 16387, 4)]
+
+
+@pytest.mark.parametrize("segs,N,R", TOPK_ROUTES)
+@pytest.mark.parametrize("kind", ["ties", "skewed", "equal", "mixed_sign"])
+def test_topk_routes_bit_exact_with_oracle(K, segs, N, R, kind):
+    """Every kernel the size rule picks, on rows with exact ties, -0 and NaN, on
+    skewed positive scores, on equal ones and on scores of both signs over many
+    binades (first digits across the whole histogram)."""
+    rng = np.random.default_rng(N + R)
+    L, B, Hkv = segs
+    if L * B * Hkv > 8 and kind in ("equal", "mixed_sign"):
+        pytest.skip("the kinds differ per kernel, not per segment")
+    W = 32
+    score, roles = np.zeros((L, B, Hkv, N), dtype=np.float32), np.zeros((B, N), dtype=np.int8)
+    for b in range(B):
+        _, roles[b] = _random_selection_case(rng, N, R + 1, R)
+    for i in np.ndindex(L, B, Hkv):
+        if kind == "ties":
+            score[i], _ = _random_selection_case(rng, N, R, R)
+        elif kind == "skewed":
+            score[i] = np.repeat(np.exp(rng.standard_normal(N // 3 + 1)), 3)[:N]
+        elif kind == "equal":
+            score[i] = 0.25
+        else:
+            score[i] = (rng.standard_normal(N) * 2.0 ** rng.integers(-100, 100, N)).astype(np.float32)
+    quota = rng.integers(1, max(2, N // (4 * R)), (B, R)).astype(np.int32)
+    _topk_check(K, score, roles, quota, W, R)
+
+
 @pytest.mark.parametrize("N,W", [(1, 0), (1, 1), (2, 0), (2, 1), (3, 3), (17, 0), (17, 5), (16, 16)])
 def test_topk_very_short_rows(K, N, W):
     """Rows shorter than one 16-position span, a row that is all window, and a
