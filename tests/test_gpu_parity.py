@@ -1053,6 +1053,29 @@ def test_decode_matches_oracle(K, case):
             assert not out[idx[0], idx[1], idx[2] * G:(idx[2] + 1) * G].any()
 
 
+@pytest.mark.parametrize("Hq,Hkv,k_cap,d,dt", [
+    (4, 1, 128, 128, "bf16"),      # one split per segment: no merge
+    (3, 1, 16 * 128, 64, "f32"),   # 16 splits: one wave per row
+    (8, 1, 17 * 128, 128, "bf16"),  # 17: four waves per row, shares of 4 and 5
+    (6, 2, 80 * 128 + 5, 64, "bf16"),
+    (2, 1, 300 * 128, 128, "f32")])  # shares of 75: more than one 64-split step per wave
+def test_decode_merge_of_many_splits(K, Hq, Hkv, k_cap, d, dt):
+    """The merge of the splits at the edges of its forms, with empty splits
+    past a short count."""
+    note(f"decode merge {Hq} {Hkv} {k_cap} {d} {dt}")
+    tdt = torch.bfloat16 if dt == "bf16" else torch.float32
+    g = torch.Generator().manual_seed(k_cap)
+    B = 2
+    q = (2.0 * torch.randn((1, B, Hq, d), generator=g)).to(tdt)
+    kc, vc = (torch.randn((1, B, Hkv, k_cap, d), generator=g).to(tdt) for _ in range(2))
+    count = np.full((1, B, Hkv), k_cap, dtype=np.int32)
+    count[0, 1] = k_cap // 3 + 1
+    out = K.decode_attention(q.cuda(), kc.cuda(), vc.cuda(), torch.from_numpy(count).cuda())
+    torch.cuda.synchronize()
+    ref, ref_abs, xmax = _decode_ref(f64(q), f64(kc), f64(vc), count)
+    check_decode(out.cpu().numpy(), ref, ref_abs, xmax, f"decode merge {k_cap}")
+
+
 def test_decode_explicit_scale_and_repeat(K):
     L, B, Hq, Hkv, k_cap, d = 1, 2, 8, 2, 400, 128
     g = torch.Generator(device="cpu")
