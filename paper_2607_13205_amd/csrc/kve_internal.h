@@ -65,9 +65,16 @@ inline DecodePlan decode_plan(int L, int B, int Hq, int Hkv, int k_cap, int d) {
 // One-shot Quest analogue: a first step writes each head's mean window query
 // (the workspace, [segs, G, d] float32); the page step cuts the prefix of a
 // segment into pages and gives each workgroup a range of whole wave steps of
-// pages (about kQuestTargetGroups workgroups in all).
+// pages: up to kQuestMaxSteps, fewer where that left under kQuestMinGroups
+// workgroups.  A workgroup's start (the mean queries, the first pages' latency)
+// is spread over its steps, and more steps than four only lengthen the tail:
+// 1 layer of 131072 keys (8 KV heads, d = 128, bf16) takes 82 us at one step
+// per workgroup, 55 at two, 50 at four and at eight; 4 x 2 x 24571 keys 79 at
+// two, 71 at four, 73 at eight; 32 x 4 x 32768 keys 1394 at four, 1457 at 16.
+// 1 layer of 8192 keys: 12.8 us at one or two, 15.4 at four (64 workgroups).
 // ---------------------------------------------------------------------------
-constexpr int kQuestTargetGroups = 4096;
+constexpr int kQuestMinGroups = 1024;
+constexpr int kQuestMaxSteps = 4;
 constexpr int kQuestMaxGroup = 8;  // query heads per KV head
 constexpr int kQuestMaxPage = 1024;
 
@@ -84,7 +91,9 @@ inline QuestPlan quest_plan(int L, int B, int Hq, int Hkv, int N, int W, int d, 
     p.n_pages = (P + page - 1) / page;
     const int step = 4 * (64 / (d * elem / 16));  // pages per workgroup step: 4 waves
     const long long steps = (p.n_pages + step - 1) / step;
-    long long per = (steps * p.segs + kQuestTargetGroups - 1) / kQuestTargetGroups;
+    long long per = steps * p.segs / kQuestMinGroups;
+    const int most = page < 16 ? kQuestMaxSteps * 16 / page : kQuestMaxSteps;  // short pages: as many keys
+    if (per > most) per = most;
     if (per < 1) per = 1;
     p.range_pages = (int)(per * step);
     p.nranges = p.n_pages > 0 ? (int)((p.n_pages + p.range_pages - 1) / p.range_pages) : 1;
