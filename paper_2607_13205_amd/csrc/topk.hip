@@ -983,6 +983,10 @@ constexpr int kCompactRows = 64;
 // Every thread takes 64 PARTS / 256 pieces, in rounds of at most four: it
 // issues the round's index loads, then its row loads, then its stores, so that
 // a block waits for memory about twice per round instead of once per piece.
+// Every row is read once and written once: non-temporal loads and stores.  8
+// layers, 13108 of 65536 token-major rows each (862 MB): 169 us with cached
+// accesses, 162 with non-temporal loads, 156 with non-temporal stores, 147
+// with both (5.9 TB/s); 1024 segments, 1639 of 32768 rows: 333 and 301 us.
 template <int PARTS>
 __global__ __launch_bounds__(kThreads) void compact_kernel(RowView kv, RowView vv_, int B, int Hkv,
                                                            const int32_t* __restrict__ idx,
@@ -1024,17 +1028,18 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(RowView kv, RowView v
             // token strides are below 2^25 bytes (checked by the caller): 32 x 32-bit products
             const unsigned piece = (unsigned)(e % PARTS) * 16u;
             const unsigned long long ko = (unsigned long long)(unsigned)tt * (unsigned)kv.s_token + piece;
-            kr[i] = ld16(k + ko);
+            kr[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(k + ko));
             if (v != nullptr)
-                vr[i] = ld16(v + (same_rows ? ko : (unsigned long long)(unsigned)tt * (unsigned)vv_.s_token + piece));
+                vr[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(
+                    v + (same_rows ? ko : (unsigned long long)(unsigned)tt * (unsigned)vv_.s_token + piece)));
         }
 #pragma unroll
         for (int i = 0; i < kRound; ++i) {
             const int e = (i0 + i) * kThreads + (int)threadIdx.x;
             if (e < total && t[i] >= 0 && t[i] < N) {
                 const size_t dst = ((size_t)seg * k_cap + m0 + e / PARTS) * kRowBytes + (size_t)(e % PARTS) * 16;
-                st16(k_out + dst, kr[i]);
-                if (v != nullptr) st16(v_out + dst, vr[i]);
+                __builtin_nontemporal_store(kr[i], reinterpret_cast<u32x4*>(k_out + dst));
+                if (v != nullptr) __builtin_nontemporal_store(vr[i], reinterpret_cast<u32x4*>(v_out + dst));
             }
         }
     }
