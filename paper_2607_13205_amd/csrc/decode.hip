@@ -110,11 +110,17 @@ __global__ __launch_bounds__(kThreads) void decode_split(const T* __restrict__ q
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int half = lane >> 5;
-    const int n = min(max(count[seg], 0), k_cap);
     const int k0 = sp * split_keys;
-    const int k1 = min(n, k0 + split_keys);
     const T* ks = kc + (size_t)seg * k_cap * D;
     const T* vs = vc + (size_t)seg * k_cap * D;
+
+    // the first step's keys do not wait for the count: rows at or past it are
+    // inside the cache and their logits are masked
+    const int blk0 = k0 + wv * kBlk;
+    typename F::frag kf[NS];
+    F::load(ks + (size_t)min(blk0 + (lane & 31), k_cap - 1) * D, half, kf);
+    const int n = min(max(count[seg], 0), k_cap);
+    const int k1 = min(n, k0 + split_keys);
 
     typename F::frag qf[NS];
     {
@@ -137,10 +143,8 @@ __global__ __launch_bounds__(kThreads) void decode_split(const T* __restrict__ q
         for (int c = 0; c < CW; ++c) o[h][c] = 0.0f;
     const int kq = lane / CPL, cg = lane - (lane / CPL) * CPL;
 
-    for (int blk = k0 + wv * kBlk; blk < k1; blk += kWaves * kBlk) {
-        // key fragments, then value pieces; row indices clamped into [0, n)
-        typename F::frag kf[NS];
-        F::load(ks + (size_t)min(blk + (lane & 31), n - 1) * D, half, kf);
+    for (int blk = blk0; blk < k1; blk += kWaves * kBlk) {
+        // value pieces, row indices clamped into [0, n)
         u32x4 vr[NV];
 #pragma unroll
         for (int i = 0; i < NV; ++i) vr[i] = ld16(vs + (size_t)min(blk + KPI * i + kq, n - 1) * D + cg * CW);
@@ -148,6 +152,10 @@ __global__ __launch_bounds__(kThreads) void decode_split(const T* __restrict__ q
         f32x16 acc = {};
 #pragma unroll
         for (int st = 0; st < NS; ++st) acc = M::mma(qf[st], kf[st], acc);
+        // the next step's keys, in flight beside the value sums (1024 segments of
+        // 1639 rows: 143.5 -> 140.5 us; float32, 64 of 5000: 70 -> 65.4)
+        if (blk + kWaves * kBlk < k1)
+            F::load(ks + (size_t)min(blk + kWaves * kBlk + (lane & 31), k_cap - 1) * D, half, kf);
 
         const bool kvalid = blk + (lane & 31) < k1;
         float x[4];
