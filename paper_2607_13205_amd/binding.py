@@ -167,7 +167,7 @@ def _dev(t, name):
         raise ValueError(f"{name} must be a device tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _view(t, name):
@@ -178,13 +178,13 @@ def _view(t, name):
     if t.dim() != 5 or (t.shape[4] > 1 and t.stride(4) != 1):
         raise ValueError(f"{name} must be 5-D with a contiguous last dimension")
     st = Strides(*(int(t.stride(i)) for i in range(4)))
-    return ctypes.c_void_p(t.data_ptr()), st
+    return t.data_ptr(), st
 
 
 def _stream(stream=None):
     torch = _torch()
     s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    return s.cuda_stream
 
 
 def _workspace(size, device, workspace=None):
@@ -201,7 +201,7 @@ def _workspace(size, device, workspace=None):
 
 
 def _ptr(t):
-    return ctypes.c_void_p(0 if t is None else t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 # ---------------------------------------------------------------------------
@@ -380,10 +380,10 @@ def role_allocate(roles, R: int, alpha, budget: float, W: int):
     quota = np.zeros((B, R), dtype=np.int32)
     kept = np.zeros(B, dtype=np.int32)
     kcap = ctypes.c_int32(0)
-    _check(LIB.kve_role_allocate(roles.ctypes.data_as(ctypes.c_void_p), B, N, int(R),
-                                 alpha.ctypes.data_as(ctypes.c_void_p), float(budget), int(W),
-                                 quota.ctypes.data_as(ctypes.c_void_p),
-                                 kept.ctypes.data_as(ctypes.c_void_p), ctypes.byref(kcap)))
+    _check(LIB.kve_role_allocate(roles.ctypes.data, B, N, int(R),
+                                 alpha.ctypes.data, float(budget), int(W),
+                                 quota.ctypes.data,
+                                 kept.ctypes.data, ctypes.byref(kcap)))
     return quota, kept, int(kcap.value)
 
 
@@ -397,10 +397,10 @@ def role_allocate_fair(roles, R: int, budget: float, W: int):
     quota = np.zeros((B, R), dtype=np.int32)
     kept = np.zeros(B, dtype=np.int32)
     kcap = ctypes.c_int32(0)
-    _check(LIB.kve_role_allocate_fair(roles.ctypes.data_as(ctypes.c_void_p), B, N, int(R),
+    _check(LIB.kve_role_allocate_fair(roles.ctypes.data, B, N, int(R),
                                       float(budget), int(W),
-                                      quota.ctypes.data_as(ctypes.c_void_p),
-                                      kept.ctypes.data_as(ctypes.c_void_p), ctypes.byref(kcap)))
+                                      quota.ctypes.data,
+                                      kept.ctypes.data, ctypes.byref(kcap)))
     return quota, kept, int(kcap.value)
 
 
@@ -411,9 +411,9 @@ def role_map(roles, bucket_of):
     if bmap.ndim != 1 or bmap.size == 0:
         raise ValueError("bucket_of must be a non-empty 1-D sequence")
     out = np.empty_like(roles)
-    _check(LIB.kve_role_map(roles.ctypes.data_as(ctypes.c_void_p), roles.size,
-                            bmap.ctypes.data_as(ctypes.c_void_p), int(bmap.size),
-                            out.ctypes.data_as(ctypes.c_void_p)))
+    _check(LIB.kve_role_map(roles.ctypes.data, roles.size,
+                            bmap.ctypes.data, int(bmap.size),
+                            out.ctypes.data))
     return out
 
 

@@ -135,24 +135,28 @@ def _fused(bufs, scorer, lse_win):
     return bufs.hist is not None and scorer == "snapkv" and lse_win is None
 
 
+def _part(t, l0, l1):
+    """Layers [l0, l1) of t: t itself when they are all of them (a slice is a
+    new tensor object, about 1.5 us of host time, and a step would make 12)."""
+    return t if t is None or (l0 == 0 and l1 == t.shape[0]) else t[l0:l1]
+
+
 def _score(q, k, bufs, scorer, pool_k, scale, page, l0, l1, stream=None, lse_win=None, roles_dev=None, R=0):
     """Score layers [l0, l1) into bufs.score[l0:l1] on ``stream`` (None: current);
     with the fused role epilogue also their role histograms."""
+    q, k, score = _part(q, l0, l1), _part(k, l0, l1), _part(bufs.score, l0, l1)
     if _fused(bufs, scorer, lse_win):
-        kb.snapkv_score_hist(q[l0:l1], k[l0:l1], roles_dev, R, pool_k, scale, score=bufs.score[l0:l1],
-                             hist=bufs.hist[l0:l1], workspace=bufs.ws_score, stream=stream)
+        kb.snapkv_score_hist(q, k, roles_dev, R, pool_k, scale, score=score, hist=_part(bufs.hist, l0, l1),
+                             workspace=bufs.ws_score, stream=stream)
     elif scorer == "snapkv" and lse_win is not None:
-        kb.snapkv_score_lse(q[l0:l1], k[l0:l1], lse_win[l0:l1], pool_k, scale, score=bufs.score[l0:l1],
-                            workspace=bufs.ws_score, stream=stream)
+        kb.snapkv_score_lse(q, k, _part(lse_win, l0, l1), pool_k, scale, score=score, workspace=bufs.ws_score,
+                            stream=stream)
     elif scorer == "snapkv":
-        kb.snapkv_score(q[l0:l1], k[l0:l1], pool_k, scale, score=bufs.score[l0:l1],
-                        workspace=bufs.ws_score, stream=stream)
+        kb.snapkv_score(q, k, pool_k, scale, score=score, workspace=bufs.ws_score, stream=stream)
     elif scorer == "quest":
-        kb.quest_score(q[l0:l1], k[l0:l1], page, score=bufs.score[l0:l1], workspace=bufs.ws_score,
-                       stream=stream)
+        kb.quest_score(q, k, page, score=score, workspace=bufs.ws_score, stream=stream)
     else:
-        kb.h2o_score(q[l0:l1], k[l0:l1], scale, score=bufs.score[l0:l1], workspace=bufs.ws_score,
-                     stream=stream)
+        kb.h2o_score(q, k, scale, score=score, workspace=bufs.ws_score, stream=stream)
 
 
 def _select(k, v, roles_dev, bufs, W, R, l0, l1, stream=None, events=None, fused=False):
@@ -160,28 +164,26 @@ def _select(k, v, roles_dev, bufs, W, R, l0, l1, stream=None, events=None, fused
     ``events``, three torch.cuda.Event, are recorded before the top-k, between
     the two calls and after the compaction.  fused: the score call counted the
     first digit (bufs.hist)."""
+    score, idx, count = _part(bufs.score, l0, l1), _part(bufs.idx, l0, l1), _part(bufs.count, l0, l1)
     if events is not None:
         events[0].record(stream)
     if fused:
-        kb.topk_select_hist(bufs.score[l0:l1], roles_dev, bufs.quota_dev, bufs.hist[l0:l1], W, R, bufs.k_cap,
-                            idx_out=bufs.idx[l0:l1], count_out=bufs.count[l0:l1], workspace=bufs.ws_topk,
-                            stream=stream)
+        kb.topk_select_hist(score, roles_dev, bufs.quota_dev, _part(bufs.hist, l0, l1), W, R, bufs.k_cap,
+                            idx_out=idx, count_out=count, workspace=bufs.ws_topk, stream=stream)
     else:
-        kb.topk_select(bufs.score[l0:l1], roles_dev, bufs.quota_dev, W, R, bufs.k_cap,
-                       idx_out=bufs.idx[l0:l1], count_out=bufs.count[l0:l1], workspace=bufs.ws_topk,
-                       stream=stream)
+        kb.topk_select(score, roles_dev, bufs.quota_dev, W, R, bufs.k_cap, idx_out=idx, count_out=count,
+                       workspace=bufs.ws_topk, stream=stream)
     if events is not None:
         events[1].record(stream)
-    kb.kv_compact(k[l0:l1], None if v is None else v[l0:l1], bufs.idx[l0:l1], bufs.count[l0:l1],
-                  k_out=bufs.k_out[l0:l1], v_out=None if bufs.v_out is None else bufs.v_out[l0:l1],
-                  stream=stream)
+    kb.kv_compact(_part(k, l0, l1), _part(v, l0, l1), idx, count, k_out=_part(bufs.k_out, l0, l1),
+                  v_out=_part(bufs.v_out, l0, l1), stream=stream)
     if events is not None:
         events[2].record(stream)
 
 
-def _upload_quotas(policy, roles_host, budget, W, bufs):
+def _upload_quotas(policy, roles_host, budget, W, bufs, stream):
     """Work out the quotas on the host and queue their upload (pinned host
-    buffer to device) on the current stream; returns (quota, kept)."""
+    buffer to device) on ``stream``, the current one; returns (quota, kept)."""
     import torch
     quota, kept, k_cap = policy.allocate(roles_host, budget, W)
     if k_cap > bufs.k_cap:
@@ -191,7 +193,7 @@ def _upload_quotas(policy, roles_host, budget, W, bufs):
     bufs.copy_done.synchronize()          # the previous upload has left quota_host
     bufs.quota_host.numpy()[...] = quota
     bufs.quota_dev.copy_(bufs.quota_host, non_blocking=True)
-    bufs.copy_done.record()
+    bufs.copy_done.record(stream)
     return quota, kept
 
 
@@ -235,10 +237,10 @@ def evict(q, k, v, roles_host: np.ndarray, roles_dev, policy, budget: float, W: 
                R=R)
         if score_events is not None:
             score_events[1].record(main)
-        quota, kept = _upload_quotas(policy, roles_host, budget, W, bufs)
+        quota, kept = _upload_quotas(policy, roles_host, budget, W, bufs, main)
         _select(k, v, roles_dev, bufs, W, R, 0, L, stream=main, events=select_events, fused=fused)
         return quota, kept
-    quota, kept = _upload_quotas(policy, roles_host, budget, W, bufs)
+    quota, kept = _upload_quotas(policy, roles_host, budget, W, bufs, main)
     side_stream.wait_stream(main)         # the quota upload and earlier work
     per = (L + chunks - 1) // chunks
     if score_events is not None:
