@@ -21,8 +21,9 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 constexpr int kSnapRowsPerGroup = 128;
 constexpr int kSnapMaxRows = 1024;
 constexpr int kSnapChunkKeys = 64;
-constexpr int kSnapTargetGroups = 4096;  // workgroups per pass the range size aims at
+constexpr int kSnapTargetGroups = 4096;  // most workgroups per pass that the range size aims at
 constexpr int kSnapMaxRangeChunks = 128;  // at most 8192 keys per range
+constexpr int kSnapCus = 256;             // compute units the ranges are balanced over
 
 // Fused role epilogue: per (segment, bucket), the number of candidate
 // positions by the top kRoleHistBits bits of their order-preserving score key
@@ -47,6 +48,40 @@ inline int role_hist_tiles(int N) { return (N + kRoleHistTile - 1) / kRoleHistTi
 // point uses as its workspace (one copy per GPU, held until the process ends).
 constexpr size_t kSnapScratchBytes = (size_t)64 << 20;
 
+// Chunks per range.  A workgroup's start (its queries' fragments, the first
+// chunk's latency) costs about four chunks of its time, and a pass ends when
+// the fullest compute unit does: of the range sizes that give at most k
+// workgroups per unit, k = 1 .. 16, the one with the least
+//   ceil(workgroups / units) (chunks per range + 4)
+// is taken, a single workgroup per unit counting its chunks 1.25 times (nothing
+// hides its latencies).  `least` is the range size that gives
+// kSnapTargetGroups workgroups: shorter ranges never pay, and from
+// kSnapMaxRangeChunks on it stands, the chip being full either way.
+// Measured as a score call with `least` and with the rule (32 heads over 8,
+// d = 128, bf16): 1 layer, N = 8192, W = 32: 24.8 -> 23.5 us; N = 32768: 60.7
+// -> 43.6; N = 131072, W = 64: 240 -> 158; 4 layers, N = 20011: 104 -> 88;
+// 8 layers x 2, N = 20011: 285 -> 252 us.
+inline long long snap_range_chunks(long long chunks, long long vsegs, long long least) {
+    if (least >= kSnapMaxRangeChunks) return least;
+    long long best = least;
+    double cost = -1.0;
+    for (int k = 1; k <= 16; ++k) {
+        long long nr = (long long)kSnapCus * k / vsegs;
+        if (nr < 1) continue;
+        if (nr > chunks) nr = chunks;
+        const long long per = (chunks + nr - 1) / nr;
+        if (per < least) break;
+        if (per > kSnapMaxRangeChunks) continue;
+        const long long rounds = (vsegs * ((chunks + per - 1) / per) + kSnapCus - 1) / kSnapCus;
+        const double c = (double)rounds * ((rounds == 1 ? 1.25 : 1.0) * (double)per + 4.0);
+        if (cost < 0.0 || c < cost) {
+            cost = c;
+            best = per;
+        }
+    }
+    return best;
+}
+
 struct SnapPlan {
     int segs, rows, sets, rpg, rgroups, n_vsegs, range_keys, nranges, planes;
     size_t off_stats, off_lse, off_raw, total;
@@ -63,12 +98,9 @@ inline SnapPlan snap_plan(int L, int B, int Hq, int Hkv, int N, int W, int d, in
     p.rgroups = (p.rows + p.rpg - 1) / p.rpg;
     p.n_vsegs = p.segs * p.rgroups;
     p.planes = p.rgroups;
-    // whole chunks per range: about kSnapTargetGroups workgroups per pass, at
-    // most 128 chunks each (longer ranges start fewer workgroups, whose query
-    // fragments and first chunks are latency before any product), and at least as many
-    // keys as the group has query rows (a workgroup loads its rows' queries
-    // once, so its keys should outweigh them); short problems thus get short
-    // ranges rather than a few workgroups walking many chunks in turn
+    // whole chunks per range: at least what gives kSnapTargetGroups workgroups
+    // per pass and as many keys as the group has query rows (a workgroup loads
+    // its rows' queries once, so its keys should outweigh them)
     const long long chunks = (N + kSnapChunkKeys - 1) / kSnapChunkKeys;
     long long per = (chunks * p.n_vsegs + kSnapTargetGroups - 1) / kSnapTargetGroups;
     const int group_rows = p.rows < p.rpg ? p.rows : p.rpg;
@@ -76,11 +108,15 @@ inline SnapPlan snap_plan(int L, int B, int Hq, int Hkv, int N, int W, int d, in
     if (per < min_per) per = min_per;
     if (per > kSnapMaxRangeChunks) per = kSnapMaxRangeChunks;
     if (per > chunks) per = chunks;
+    // the workspace holds the statistics of the smallest ranges: its size does
+    // not depend on how the rule below balances them
+    const size_t stats_ranges = (size_t)((chunks + per - 1) / per);
+    per = snap_range_chunks(chunks, p.n_vsegs, per);
     p.range_keys = (int)(per * kSnapChunkKeys);
     p.nranges = (int)((chunks + per - 1) / per);
     size_t off = 0;
     p.off_stats = off;
-    off = align_up(off + (size_t)p.n_vsegs * p.nranges * p.rpg * sizeof(float));
+    off = align_up(off + (size_t)p.n_vsegs * stats_ranges * p.rpg * sizeof(float));
     p.off_lse = off;
     off = align_up(off + (size_t)p.n_vsegs * p.rpg * sizeof(float));
     p.off_raw = off;

@@ -55,6 +55,7 @@ constexpr int kKeys = kSnapChunkKeys;  // keys per chunk
 // as few as the top-k reads)
 constexpr int kPoolTile = 2048;
 constexpr int kMaxPoolHalf = 127;
+constexpr int kMergeRanges = 32;  // ranges up to which pass 2 merges the row statistics itself
 
 // LDS ring depth and workgroups per compute unit of each pass.  bf16: both
 // passes keep one chunk in flight at four workgroups per CU (with non-temporal
@@ -238,33 +239,39 @@ __global__ __launch_bounds__(kThreads, (sizeof(T) == 4 && D == 128 ? 1 : TuneRS<
     }
 }
 
-// Four threads per row of a row group (thread 4 r + s, rpg = blockDim.x / 4
-// rows): thread s merges every fourth range from range s, 32 ranges' values
-// loaded before any is merged, then the four partial sums of a row merge by
-// shuffles.
+// log2 of a row's softmax denominator from its ranges' values (v0[c * pitch],
+// c < nranges): SPLIT threads per row, adjacent lanes; thread `sub` merges
+// every SPLIT-th range, 32 ranges' values loaded before any is merged, then
+// the partial sums merge by shuffles.  +inf for a row without a visible key.
+template <int SPLIT>
+__device__ __forceinline__ float merge_ranges(const float* v0, int nranges, int pitch, int sub) {
+    float a = -INFINITY, b = 0.0f;
+    for (int c0 = sub; c0 < nranges; c0 += 32 * SPLIT) {
+        float v[32];
+#pragma unroll
+        for (int j = 0; j < 32; ++j) v[j] = v0[(size_t)min(c0 + j * SPLIT, nranges - 1) * pitch];
+#pragma unroll
+        for (int j = 0; j < 32; ++j)
+            if (c0 + j * SPLIT < nranges) lse2_merge(a, b, v[j], v[j] == -INFINITY ? 0.0f : 1.0f);
+    }
+#pragma unroll
+    for (int m = 1; m < SPLIT; m <<= 1) {
+        const float ao = __shfl_xor(a, m), bo = __shfl_xor(b, m);
+        lse2_merge(a, b, ao, bo);
+    }
+    return b > 0.0f ? a + log2f(b) : INFINITY;
+}
+
+// Four threads per row of a row group (thread 4 r + s, rpg = blockDim.x / 4 rows).
 constexpr int kCombineSplit = 4;
 __global__ __launch_bounds__(2 * kSnapRowsPerGroup * kCombineSplit) void snap_combine(
     const float* __restrict__ stats, int nranges, int rows, int rgroups, float* __restrict__ lse) {
     const int vseg = blockIdx.x, rpg = blockDim.x / kCombineSplit;
     const int r = threadIdx.x / kCombineSplit, sub = threadIdx.x % kCombineSplit;
     const int row = (vseg % rgroups) * rpg + r;
-    float a = -INFINITY, b = 0.0f;
-    for (int c0 = sub; c0 < nranges; c0 += 32 * kCombineSplit) {
-        float v[32];
-#pragma unroll
-        for (int j = 0; j < 32; ++j)
-            v[j] = stats[((size_t)vseg * nranges + min(c0 + j * kCombineSplit, nranges - 1)) * rpg + r];
-#pragma unroll
-        for (int j = 0; j < 32; ++j)
-            if (c0 + j * kCombineSplit < nranges) lse2_merge(a, b, v[j], v[j] == -INFINITY ? 0.0f : 1.0f);
-    }
-#pragma unroll
-    for (int m = 1; m < kCombineSplit; m <<= 1) {
-        const float ao = __shfl_xor(a, m), bo = __shfl_xor(b, m);
-        lse2_merge(a, b, ao, bo);
-    }
+    const float l2 = merge_ranges<kCombineSplit>(stats + (size_t)vseg * nranges * rpg + r, nranges, rpg, sub);
     // rows past the window rows contribute nothing to the column sums
-    if (sub == 0) lse[(size_t)vseg * rpg + r] = (row < rows && b > 0.0f) ? a + log2f(b) : INFINITY;
+    if (sub == 0) lse[(size_t)vseg * rpg + r] = row < rows ? l2 : INFINITY;
 }
 
 // Row statistics supplied by the caller (the natural-log log-sum-exp of each
@@ -284,7 +291,7 @@ __global__ __launch_bounds__(2 * kSnapRowsPerGroup) void snap_import_lse(const f
 template <typename T, int D, int RS>
 __global__ __launch_bounds__(kThreads, (sizeof(T) == 4 && D == 128 ? 1 : TuneRS<T, RS>::kOcc2)) void snap_pass2(
     RowView qv, RowView kv, int B, int Hkv, int N, int W, int rows, int rgroups, int nranges, int range_keys,
-    float sl2, const float* __restrict__ lse, int segs, float* __restrict__ raw) {
+    float sl2, const float* __restrict__ lse, const float* __restrict__ stats, int segs, float* __restrict__ raw) {
     constexpr int kRing = TuneRS<T, RS>::kRing2;
     constexpr int kRpg = RS * kSnapRowsPerGroup;
     using G = Geo<T, D, kRing>;
@@ -303,9 +310,23 @@ __global__ __launch_bounds__(kThreads, (sizeof(T) == 4 && D == 128 ? 1 : TuneRS<
     // exactly 0.  The window index of each row stays in LDS for the masked
     // path: as registers the 32 loop-invariant bounds would stay live across
     // the whole loop.
-    for (int r = threadIdx.x; r < kRpg; r += kThreads) {
-        sinit[r] = -lse[(size_t)sp.vseg * kRpg + r] / sl2;
-        swin[r] = (sp.rg * kRpg + r) % W;
+    // With stats given (few ranges) the workgroup merges its rows' range values
+    // itself, as snap_combine does, kPerRow threads per row.
+    constexpr int kPerRow = kThreads / kRpg;
+    {
+        const int r = threadIdx.x / kPerRow, sub = threadIdx.x % kPerRow;
+        const int row = sp.rg * kRpg + r;
+        float l2;
+        if (stats != nullptr) {
+            l2 = merge_ranges<kPerRow>(stats + (size_t)sp.vseg * nranges * kRpg + r, nranges, kRpg, sub);
+            if (row >= rows) l2 = INFINITY;
+        } else {
+            l2 = lse[(size_t)sp.vseg * kRpg + r];
+        }
+        if (sub == 0) {
+            sinit[r] = -l2 / sl2;
+            swin[r] = row % W;
+        }
     }
     // wave w holds rows 32 RS w .. 32 RS (w + 1) - 1 of the row group, in RS sets of 32
     const char* qseg = seg_rows(qv, sp.seg, B, Hkv, rows / W);
@@ -603,18 +624,20 @@ template <typename T, int D, int RS>
 void launch_passes(const RowView& qv, const RowView& kv, int B, int Hkv, const float* lse_win, const SnapPlan& p,
                    int N, int W, float sl2, float* stats, float* lse, float* raw, hipStream_t st) {
     const dim3 grid((unsigned)((size_t)p.n_vsegs * p.nranges));
+    bool merge = false;  // pass 2 merges the ranges itself
     if (lse_win != nullptr) {  // row statistics from the caller: one read of K
         hipLaunchKernelGGL(snap_import_lse, dim3((unsigned)p.n_vsegs), dim3(p.rpg), 0, st, lse_win, p.rows,
                            p.rgroups, lse);
     } else {
         hipLaunchKernelGGL((snap_pass1<T, D, RS>), grid, dim3(kThreads), 0, st, qv, kv, B, Hkv, N, W, p.rows,
                            p.rgroups, p.nranges, p.range_keys, sl2, stats);
-        hipLaunchKernelGGL(snap_combine, dim3((unsigned)p.n_vsegs), dim3(p.rpg * kCombineSplit), 0, st, stats,
-                           p.nranges, p.rows,
-                           p.rgroups, lse);
+        merge = p.nranges <= kMergeRanges;
+        if (!merge)
+            hipLaunchKernelGGL(snap_combine, dim3((unsigned)p.n_vsegs), dim3(p.rpg * kCombineSplit), 0, st, stats,
+                               p.nranges, p.rows, p.rgroups, lse);
     }
     hipLaunchKernelGGL((snap_pass2<T, D, RS>), grid, dim3(kThreads), 0, st, qv, kv, B, Hkv, N, W, p.rows,
-                       p.rgroups, p.nranges, p.range_keys, sl2, lse, p.segs, raw);
+                       p.rgroups, p.nranges, p.range_keys, sl2, lse, merge ? stats : nullptr, p.segs, raw);
 }
 
 template <typename T, int D>
