@@ -36,6 +36,7 @@
 #include "kve_device.h"
 #include "kve_internal.h"
 #include "kve_snap_plan.h"
+#include "kve_split.h"
 #include "kve_stream.h"
 
 // Workspace of the allocation-free entry point: a static device array, one
@@ -63,14 +64,8 @@ constexpr int kMergeRanges = 32;  // ranges up to which pass 2 merges the row st
 // than a second chunk ahead: measured 1-2% faster than two chunks at three);
 // the extra workgroup also overlaps more of one wave's exponentials with
 // another's products.
-// fp32 fragments need twice the registers: two workgroups, three chunks ahead
-// (one workgroup at d = 128, whose 32 KB chunks fill LDS with the ring).
-template <typename T>
+template <int RS>
 struct Tune {
-    static constexpr int kRing1 = 4, kOcc1 = 2, kRing2 = 4, kOcc2 = 2;
-};
-template <>
-struct Tune<__bf16> {
     static constexpr int kRing1 = 2, kOcc1 = 4, kRing2 = 2, kOcc2 = 4;
 };
 // two 32-row sets per wave (bf16, windows of more than 128 rows): twice the
@@ -79,10 +74,8 @@ struct Tune<__bf16> {
 // 2 reads its start values from LDS into the accumulators at every chunk
 // (4-5% faster per pass than two workgroups on the 32-layer, N = 131072,
 // W = 64 workload)
-template <typename T, int RS>
-struct TuneRS : Tune<T> {};
-template <typename T>
-struct TuneRS<T, 2> {
+template <>
+struct Tune<2> {
     static constexpr int kRing1 = 3, kOcc1 = 3, kRing2 = 3, kOcc2 = 3;
 };
 
@@ -164,10 +157,10 @@ struct KeyChunks {
 };
 
 template <typename T, int D, int RS>
-__global__ __launch_bounds__(kThreads, (sizeof(T) == 4 && D == 128 ? 1 : TuneRS<T, RS>::kOcc1)) void snap_pass1(
+__global__ __launch_bounds__(kThreads, Tune<RS>::kOcc1) void snap_pass1(
     RowView qv, RowView kv, int B, int Hkv, int N, int W, int rows, int rgroups, int nranges, int range_keys,
     float sl2, float* __restrict__ stats) {
-    constexpr int kRing = TuneRS<T, RS>::kRing1;
+    constexpr int kRing = Tune<RS>::kRing1;
     constexpr int kRpg = RS * kSnapRowsPerGroup;
     using G = Geo<T, D, kRing>;
     __shared__ __align__(16) char ring[kRing * G::C::BYTES];
@@ -262,6 +255,17 @@ __device__ __forceinline__ float merge_ranges(const float* v0, int nranges, int 
     return b > 0.0f ? a + log2f(b) : INFINITY;
 }
 
+// A row's log-sum-exp for pass 2 (SPLIT threads per row): merged here from
+// the ranges' values when stats is given, else as snap_combine or the import
+// step left it.  +inf for rows past the window rows.
+template <int SPLIT>
+__device__ __forceinline__ float row_lse2(const float* lse, const float* stats, int vseg, int nranges, int rpg, int r,
+                                          int sub, bool valid) {
+    if (stats == nullptr) return lse[(size_t)vseg * rpg + r];
+    const float l2 = merge_ranges<SPLIT>(stats + (size_t)vseg * nranges * rpg + r, nranges, rpg, sub);
+    return valid ? l2 : INFINITY;
+}
+
 // Four threads per row of a row group (thread 4 r + s, rpg = blockDim.x / 4 rows).
 constexpr int kCombineSplit = 4;
 __global__ __launch_bounds__(2 * kSnapRowsPerGroup * kCombineSplit) void snap_combine(
@@ -289,10 +293,10 @@ __global__ __launch_bounds__(2 * kSnapRowsPerGroup) void snap_import_lse(const f
 }
 
 template <typename T, int D, int RS>
-__global__ __launch_bounds__(kThreads, (sizeof(T) == 4 && D == 128 ? 1 : TuneRS<T, RS>::kOcc2)) void snap_pass2(
+__global__ __launch_bounds__(kThreads, Tune<RS>::kOcc2) void snap_pass2(
     RowView qv, RowView kv, int B, int Hkv, int N, int W, int rows, int rgroups, int nranges, int range_keys,
     float sl2, const float* __restrict__ lse, const float* __restrict__ stats, int segs, float* __restrict__ raw) {
-    constexpr int kRing = TuneRS<T, RS>::kRing2;
+    constexpr int kRing = Tune<RS>::kRing2;
     constexpr int kRpg = RS * kSnapRowsPerGroup;
     using G = Geo<T, D, kRing>;
     __shared__ __align__(16) char ring[kRing * G::C::BYTES];
@@ -316,13 +320,7 @@ __global__ __launch_bounds__(kThreads, (sizeof(T) == 4 && D == 128 ? 1 : TuneRS<
     {
         const int r = threadIdx.x / kPerRow, sub = threadIdx.x % kPerRow;
         const int row = sp.rg * kRpg + r;
-        float l2;
-        if (stats != nullptr) {
-            l2 = merge_ranges<kPerRow>(stats + (size_t)sp.vseg * nranges * kRpg + r, nranges, kRpg, sub);
-            if (row >= rows) l2 = INFINITY;
-        } else {
-            l2 = lse[(size_t)sp.vseg * kRpg + r];
-        }
+        const float l2 = row_lse2<kPerRow>(lse, stats, sp.vseg, nranges, kRpg, r, sub, row < rows);
         if (sub == 0) {
             sinit[r] = -l2 / sl2;
             swin[r] = row % W;
@@ -439,6 +437,221 @@ __global__ __launch_bounds__(kThreads, (sizeof(T) == 4 && D == 128 ? 1 : TuneRS<
             interleave_trans<32 * RS>();
             scol[s & 1][lane][wave] = lane < 32 ? v[0] : v[1];
         }
+    }
+    __syncthreads();
+    reduce(sp.nch - 1);
+}
+
+// float32 passes: rows split into float16 pairs (kve_split.h), three 16-bit
+// products per float32 one, in the tiling of the one-set bf16 passes: a wave
+// holds 32 query rows as fragments, 64-key chunks stream.  A chunk lands in LDS
+// as float32, each wave splits a quarter of it into the two planes the products
+// read, and the next chunk's loads go out once every wave has read the raw
+// slot, so that they are in flight beside the products.  64.5 KB of LDS at
+// d = 128: two workgroups per CU.
+template <int D>
+struct SplitLds {
+    using S = SplitChunk<D>;
+    __align__(16) char raw[S::Raw::BYTES];
+    __align__(16) char hi[S::PLANE];
+    __align__(16) char lo[S::PLANE];
+    __align__(16) float unscale[kKeys];
+};
+template <int D>
+using SplitWr = ChunkWriter<float, D, kKeys, kWaves, true>;
+
+// Fragments of this lane's query row (zero past the window rows); returns its unscale.
+template <int D>
+__device__ __forceinline__ float load_q_split(typename SplitChunk<D>::Frags& qf, const char* qseg, const RowView& qv,
+                                              int rows, int W, int row, int lane) {
+    const int r = row < rows ? row : 0;
+    return SplitChunk<D>::load_row(qf, qseg + (long long)(r / W) * qv.s_head + (long long)(r % W) * qv.s_token,
+                                   row < rows, lane);
+}
+
+template <int D>
+__global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void snap_pass1_f32(
+    RowView qv, RowView kv, int B, int Hkv, int N, int W, int rows, int rgroups, int nranges, int range_keys,
+    float sl2, float* __restrict__ stats) {
+    using S = SplitChunk<D>;
+    __shared__ SplitLds<D> sh;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const Span sp = span_of(nranges, rgroups, range_keys, N);
+    const int P_rows = N - W;
+    const KeyChunks<float, D> src{seg_rows(kv, sp.seg, B, Hkv, 1), kv.s_token, sp.t_begin, sp.t_end};
+    SplitWr<D> wr;
+    wr.init(wave, lane, (unsigned)kv.s_token);
+    auto issue = [&](int c) {
+        const char* rws;
+        int valid;
+        src(c, &rws, &valid);
+        wr.issue(sh.raw, rws, valid);
+    };
+    issue(0);
+    const int qr = sp.rg * kSnapRowsPerGroup + wave * 32 + (lane & 31);  // this lane's query row
+    typename S::Frags qf[1];
+    const float ls = sl2 * load_q_split<D>(qf[0], seg_rows(qv, sp.seg, B, Hkv, rows / W), qv, rows, W, qr, lane);
+    const int lim = qr < rows ? P_rows + qr % W : -1;  // last key the row sees
+
+    RowSum rsum[1];
+#pragma unroll 1
+    for (int s = 0; s < sp.nch; ++s) {
+        wait_vmcnt<0>();
+        lds_barrier();  // chunk s landed; every wave is done with the planes of chunk s - 1
+        S::convert(sh.raw, sh.hi, sh.lo, sh.unscale, wave, lane);
+        lds_barrier();  // planes written, raw slot read
+        if (s + 1 < sp.nch) issue(s + 1);
+        float ln[1];
+        // a second round, of the whole wave, when a sum left [0, 2^64]: the
+        // exponentials replaced the logits, and the planes stay until the next
+        // barrier
+#pragma unroll 1
+        for (bool again = false;; again = true) {
+            f32x16 acc[1][2];
+            S::template mma<true, 1>(acc, sh.hi, sh.lo, qf, lane);
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {
+                    const float4 v = *reinterpret_cast<const float4*>(sh.unscale + 32 * b + c_row(4 * a, lane));
+                    const float u[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[0][b][4 * a + e] *= u[e] * ls;
+                }
+            if (sp.t_begin + (s + 1) * kKeys > min(P_rows, sp.t_end)) {  // past the range end or inside the window
+                const int last = min(lim, sp.t_end - 1) - (sp.t_begin + s * kKeys + 4 * (lane >> 5));
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i)
+                        acc[0][kb][i] = mask_neg(acc[0][kb][i], last - (32 * kb + 8 * (i >> 2) + (i & 3)));
+            }
+            if (again) {
+                row_sums_fix<1>(rsum, acc, 1.0f, ln);
+                break;
+            }
+            if (row_sums_try<1>(rsum, acc, 1.0f, ln)) break;
+        }
+    }
+    // the two lane halves hold the same row and different keys
+    lse2_merge(rsum[0].m, rsum[0].l, __shfl_xor(rsum[0].m, 32), __shfl_xor(rsum[0].l, 32));
+    if (lane < 32)
+        stats[((size_t)sp.vseg * nranges + sp.range) * kSnapRowsPerGroup + wave * 32 + lane] = rsum[0].lse2();
+}
+
+template <int D>
+__global__ __launch_bounds__(kThreads, 2) void snap_pass2_f32(RowView qv, RowView kv, int B, int Hkv, int N, int W,
+                                                              int rows, int rgroups, int nranges, int range_keys,
+                                                              float sl2, const float* __restrict__ lse,
+                                                              const float* __restrict__ stats, int segs,
+                                                              float* __restrict__ raw) {
+    using S = SplitChunk<D>;
+    constexpr int kRpg = kSnapRowsPerGroup;
+    __shared__ SplitLds<D> sh;
+    __shared__ __align__(16) float scol[2][kKeys][kWaves];  // column sums per key and wave, two chunks
+    __shared__ __align__(16) float sinit[kRpg];             // -lse2 of each row
+    __shared__ __align__(16) float srow[kRpg];              // unscale of each row, times sl2
+    __shared__ __align__(16) int swin[kRpg];                // window index (row % W) of each row
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const Span sp = span_of(nranges, rgroups, range_keys, N);
+    const int P_rows = N - W;
+    const KeyChunks<float, D> src{seg_rows(kv, sp.seg, B, Hkv, 1), kv.s_token, sp.t_begin, sp.t_end};
+    SplitWr<D> wr;
+    wr.init(wave, lane, (unsigned)kv.s_token);
+    auto issue = [&](int c) {
+        const char* rws;
+        int valid;
+        src(c, &rws, &valid);
+        wr.issue(sh.raw, rws, valid);
+    };
+    issue(0);
+    {
+        constexpr int kPerRow = kThreads / kRpg;
+        const int r = threadIdx.x / kPerRow, sub = threadIdx.x % kPerRow;
+        const int row = sp.rg * kRpg + r;
+        const float l2 = row_lse2<kPerRow>(lse, stats, sp.vseg, nranges, kRpg, r, sub, row < rows);
+        if (sub == 0) {
+            sinit[r] = -l2;
+            swin[r] = row % W;
+        }
+    }
+    typename S::Frags qf[1];
+    const float uq = load_q_split<D>(qf[0], seg_rows(qv, sp.seg, B, Hkv, rows / W), qv, rows, W,
+                                     sp.rg * kRpg + wave * 32 + (lane & 31), lane);
+    if (lane < 32) srow[wave * 32 + lane] = uq * sl2;
+    __syncthreads();
+    f32x16 c_init, c_scale;  // of this lane's 16 rows
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        const float4 v = *reinterpret_cast<const float4*>(&sinit[wave * 32 + c_row(4 * a, lane)]);
+        const float4 w = *reinterpret_cast<const float4*>(&srow[wave * 32 + c_row(4 * a, lane)]);
+        c_init[4 * a] = v.x;
+        c_init[4 * a + 1] = v.y;
+        c_init[4 * a + 2] = v.z;
+        c_init[4 * a + 3] = v.w;
+        c_scale[4 * a] = w.x;
+        c_scale[4 * a + 1] = w.y;
+        c_scale[4 * a + 2] = w.z;
+        c_scale[4 * a + 3] = w.w;
+    }
+    pin(c_init);
+    pin(c_scale);
+    float* out = raw + ((size_t)sp.rg * segs + sp.seg) * N;
+    // add the four waves' column sums of chunk s, as in snap_pass2
+    auto reduce = [&](int s) {
+        if (wave == (s & (kWaves - 1))) {
+            const int t = sp.t_begin + s * kKeys + lane;
+            const float4 c = *reinterpret_cast<const float4*>(&scol[s & 1][lane][0]);
+            if (t < sp.t_end) out[t] = (c.x + c.y) + (c.z + c.w);
+        }
+    };
+#pragma unroll 1
+    for (int s = 0; s < sp.nch; ++s) {
+        wait_vmcnt<0>();
+        // chunk s landed, every wave is done with the planes of chunk s - 1, and
+        // the scol writes of chunk s - 1 are there to be added
+        lds_barrier();
+        S::convert(sh.raw, sh.hi, sh.lo, sh.unscale, wave, lane);
+        if (s >= 1) reduce(s - 1);
+        lds_barrier();  // planes written, raw slot read, sums of chunk s - 1 read
+        if (s + 1 < sp.nch) issue(s + 1);
+        f32x16 acc[1][2];
+        S::template mma<false, 1>(acc, sh.hi, sh.lo, qf, lane);
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+            const float u = sh.unscale[32 * kb + (lane & 31)];  // this lane's key
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[0][kb][i] = fmaf(acc[0][kb][i], u * c_scale[i], c_init[i]);
+        }
+        if (sp.t_begin + (s + 1) * kKeys > min(P_rows, sp.t_end)) {  // past the range end or inside the window
+            // key t is visible to window query i (position P_rows + i) iff t - P_rows <= i
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                const int4 w4 = *reinterpret_cast<const int4*>(&swin[wave * 32 + c_row(4 * a, lane)]);
+                const int wv[4] = {w4.x, w4.y, w4.z, w4.w};
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb) {
+                    const int t = sp.t_begin + s * kKeys + 32 * kb + (lane & 31);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        acc[0][kb][4 * a + e] =
+                            mask_neg(acc[0][kb][4 * a + e], (sp.t_end - 1 - t) | (wv[e] - (t - P_rows)));
+                }
+            }
+        }
+        float v[2];
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+            f32x16& x = acc[0][kb];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) x[i] = fast_exp2(x[i]);
+            v[kb] = half_wave_sum(((x[0] + x[1]) + (x[2] + x[3]) + ((x[4] + x[5]) + (x[6] + x[7]))) +
+                                  (((x[8] + x[9]) + (x[10] + x[11])) + ((x[12] + x[13]) + (x[14] + x[15]))));
+        }
+        interleave_trans<32>();
+        scol[s & 1][lane][wave] = lane < 32 ? v[0] : v[1];
     }
     __syncthreads();
     reduce(sp.nch - 1);
@@ -629,15 +842,24 @@ void launch_passes(const RowView& qv, const RowView& kv, int B, int Hkv, const f
         hipLaunchKernelGGL(snap_import_lse, dim3((unsigned)p.n_vsegs), dim3(p.rpg), 0, st, lse_win, p.rows,
                            p.rgroups, lse);
     } else {
-        hipLaunchKernelGGL((snap_pass1<T, D, RS>), grid, dim3(kThreads), 0, st, qv, kv, B, Hkv, N, W, p.rows,
-                           p.rgroups, p.nranges, p.range_keys, sl2, stats);
+        if constexpr (sizeof(T) == 2)
+            hipLaunchKernelGGL((snap_pass1<T, D, RS>), grid, dim3(kThreads), 0, st, qv, kv, B, Hkv, N, W, p.rows,
+                               p.rgroups, p.nranges, p.range_keys, sl2, stats);
+        else
+            hipLaunchKernelGGL((snap_pass1_f32<D>), grid, dim3(kThreads), 0, st, qv, kv, B, Hkv, N, W, p.rows,
+                               p.rgroups, p.nranges, p.range_keys, sl2, stats);
         merge = p.nranges <= kMergeRanges;
         if (!merge)
             hipLaunchKernelGGL(snap_combine, dim3((unsigned)p.n_vsegs), dim3(p.rpg * kCombineSplit), 0, st, stats,
                                p.nranges, p.rows, p.rgroups, lse);
     }
-    hipLaunchKernelGGL((snap_pass2<T, D, RS>), grid, dim3(kThreads), 0, st, qv, kv, B, Hkv, N, W, p.rows,
-                       p.rgroups, p.nranges, p.range_keys, sl2, lse, merge ? stats : nullptr, p.segs, raw);
+    const float* ranges = merge ? stats : nullptr;
+    if constexpr (sizeof(T) == 2)
+        hipLaunchKernelGGL((snap_pass2<T, D, RS>), grid, dim3(kThreads), 0, st, qv, kv, B, Hkv, N, W, p.rows,
+                           p.rgroups, p.nranges, p.range_keys, sl2, lse, ranges, p.segs, raw);
+    else
+        hipLaunchKernelGGL((snap_pass2_f32<D>), grid, dim3(kThreads), 0, st, qv, kv, B, Hkv, N, W, p.rows, p.rgroups,
+                           p.nranges, p.range_keys, sl2, lse, ranges, p.segs, raw);
 }
 
 template <typename T, int D>

@@ -114,6 +114,37 @@ def test_snapkv_explicit_scale(K):
     check_scores(f64(score), ref, "scale")
 
 
+@pytest.mark.parametrize("N,Hq,Hkv,W,d", [(64, 1, 1, 16, 128), (65, 4, 1, 32, 128), (129, 3, 1, 16, 64),
+                                          (1000, 8, 1, 32, 64), (700, 4, 2, 64, 128), (5003, 4, 1, 8, 128)])
+@pytest.mark.parametrize("kind", ["plain", "magnitudes", "lse"])
+def test_snapkv_f32_split_matches_float64(K, N, Hq, Hkv, W, d, kind):
+    """The float32 score (rows as float16 pairs with a power of two per row)
+    against the 64-bit one, at the edges of the 64-key chunks and the ranges:
+    rows of ordinary size, rows of very different sizes whose logits are
+    ordinary, and the window statistics supplied."""
+    note(f"snapkv f32 split N={N} Hq={Hq} Hkv={Hkv} W={W} d={d} {kind}")
+    g = torch.Generator().manual_seed(N + d + W)
+    q = torch.randn((1, 1, Hq, W, d), generator=g)
+    k = torch.randn((1, 1, Hkv, N, d), generator=g)
+    if kind == "magnitudes":
+        e = torch.randint(-100, 101, (1, 1, Hkv, 1, 1), generator=g).double()
+        k = (k.double() * 2.0 ** e).float()
+        q = (q.double() * 2.0 ** -e.repeat_interleave(Hq // Hkv, dim=2)).float()
+        k[:, :, :, 1::5] *= 2.0 ** -20
+    if kind == "lse":
+        x = np.matmul(f64(q), np.repeat(f64(k), Hq // Hkv, axis=2).swapaxes(-1, -2)) * d ** -0.5
+        x = np.where(np.arange(N) > np.arange(N - W, N)[:, None], -np.inf, x)
+        lse = torch.from_numpy(np.log(np.exp(x).sum(-1))).float().cuda()
+        score = K.snapkv_score_lse(q.cuda(), k.cuda(), lse, 5)
+    else:
+        score = run_snapkv(K, q.cuda(), k.cuda(), 5)
+    torch.cuda.synchronize()
+    ref = O.snapkv_score(f64(q), f64(k), Hkv, 5)
+    tol = _f32_logit_bound(q, k, Hkv, d ** -0.5) + 3e-6  # the exponentials, a supplied lse and the sums
+    err = np.abs(f64(score) - ref)
+    assert np.all(err <= tol * np.abs(ref) + 1e-30), float((err / (np.abs(ref) + 1e-30)).max())
+
+
 # Logit spikes: every 97th key row scaled by 40, so that (with N(0, 1) inputs)
 # many rows meet a key whose logit lies more than 64, and some more than 128,
 # log2 units above the running reference of their range: the row sums leave
