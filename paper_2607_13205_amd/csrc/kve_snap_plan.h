@@ -54,14 +54,16 @@ constexpr size_t kSnapScratchBytes = (size_t)64 << 20;
 // workgroups per unit, k = 1 .. 16, the one with the least
 //   ceil(workgroups / units) (chunks per range + 4)
 // is taken, a single workgroup per unit counting its chunks 1.25 times (nothing
-// hides its latencies).  `least` is the range size that gives
+// hides its latencies; float32, whose chunks are split between barriers, 1.4
+// times: N = 32768 takes 98 us at 16 chunks, one per unit, and 90 at eight).  `least` is the range size that gives
 // kSnapTargetGroups workgroups: shorter ranges never pay, and from
 // kSnapMaxRangeChunks on it stands, the chip being full either way.
 // Measured as a score call with `least` and with the rule (32 heads over 8,
 // d = 128, bf16): 1 layer, N = 8192, W = 32: 24.8 -> 23.5 us; N = 32768: 60.7
 // -> 43.6; N = 131072, W = 64: 240 -> 158; 4 layers, N = 20011: 104 -> 88;
 // 8 layers x 2, N = 20011: 285 -> 252 us.
-inline long long snap_range_chunks(long long chunks, long long vsegs, long long least) {
+inline long long snap_range_chunks(long long chunks, long long vsegs, long long least, int elem) {
+    const double alone = elem == 4 ? 1.4 : 1.25;
     if (least >= kSnapMaxRangeChunks) return least;
     long long best = least;
     double cost = -1.0;
@@ -73,7 +75,7 @@ inline long long snap_range_chunks(long long chunks, long long vsegs, long long 
         if (per < least) break;
         if (per > kSnapMaxRangeChunks) continue;
         const long long rounds = (vsegs * ((chunks + per - 1) / per) + kSnapCus - 1) / kSnapCus;
-        const double c = (double)rounds * ((rounds == 1 ? 1.25 : 1.0) * (double)per + 4.0);
+        const double c = (double)rounds * ((rounds == 1 ? alone : 1.0) * (double)per + 4.0);
         if (cost < 0.0 || c < cost) {
             cost = c;
             best = per;
@@ -84,6 +86,7 @@ inline long long snap_range_chunks(long long chunks, long long vsegs, long long 
 
 struct SnapPlan {
     int segs, rows, sets, rpg, rgroups, n_vsegs, range_keys, nranges, planes;
+    int pair;  // a range's statistics are {reference, sum} pairs, not one log-sum-exp
     size_t off_stats, off_lse, off_raw, total;
 };
 
@@ -111,9 +114,13 @@ inline SnapPlan snap_plan(int L, int B, int Hq, int Hkv, int N, int W, int d, in
     // the workspace holds the statistics of the smallest ranges: its size does
     // not depend on how the rule below balances them
     const size_t stats_ranges = (size_t)((chunks + per - 1) / per);
-    per = snap_range_chunks(chunks, p.n_vsegs, per);
+    per = snap_range_chunks(chunks, p.n_vsegs, per, elem);
     p.range_keys = (int)(per * kSnapChunkKeys);
     p.nranges = (int)((chunks + per - 1) / per);
+    // longer ranges leave room for two floats each: the pair keeps the rounding
+    // of a log-sum-exp (2^-20 at a magnitude of 8 to 16) out of the ranges'
+    // merge, where over fewer ranges it averages out less
+    p.pair = 2 * (size_t)p.nranges <= stats_ranges;
     size_t off = 0;
     p.off_stats = off;
     off = align_up(off + (size_t)p.n_vsegs * stats_ranges * p.rpg * sizeof(float));

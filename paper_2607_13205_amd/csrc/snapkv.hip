@@ -13,7 +13,7 @@
 // fragments stay in registers.  Keys stream through an LDS
 // ring in chunks of 64 with direct-to-LDS loads issued one to three chunks
 // ahead, so every wave keeps HBM requests in flight while it multiplies on the
-// matrix cores (bf16 32x32x16, fp32 32x32x2).  No workgroup waits on another
+// matrix cores (bf16 32x32x16; float32 split into float16 pairs, kve_split.h).  No workgroup waits on another
 // one; two to four workgroups share a compute unit, so that one's matrix-core
 // work overlaps another's exponentials.
 //
@@ -21,7 +21,8 @@
 //                          32-key block, so the running row sum of
 //                          exp2(x - ref) stays in the lane; one log-sum-exp per
 //                          (vseg, range, row) is written.
-//   combine  snap_combine  per row: lse2 over the ranges (+inf for padding rows).
+//   combine  snap_combine  per row: lse2 over the ranges (+inf for padding rows);
+//                          pass 2 does it itself up to kMergeRanges ranges.
 //   pass 2   snap_pass2    S = Q K^T: each lane holds one key and 16 rows per
 //                          block, so the column sum of exp2(x - lse2) is a lane
 //                          sum plus one shuffle; the four row blocks (waves)
@@ -56,7 +57,7 @@ constexpr int kKeys = kSnapChunkKeys;  // keys per chunk
 // as few as the top-k reads)
 constexpr int kPoolTile = 2048;
 constexpr int kMaxPoolHalf = 127;
-constexpr int kMergeRanges = 32;  // ranges up to which pass 2 merges the row statistics itself
+constexpr int kMergeRanges = 64;  // ranges up to which pass 2 merges the row statistics itself
 
 // LDS ring depth and workgroups per compute unit of each pass.  bf16: both
 // passes keep one chunk in flight at four workgroups per CU (with non-temporal
@@ -156,10 +157,20 @@ struct KeyChunks {
     }
 };
 
+// A row's statistics of one range: one log-sum-exp (log2 units), or with
+// `pair` the reference and the sum as they are.
+__device__ __forceinline__ void store_stats(float* stats, size_t i, bool pair, const RowSum& r) {
+    const bool some = r.m != -INFINITY && r.l > 0.0f;
+    if (pair)
+        reinterpret_cast<float2*>(stats)[i] = some ? make_float2(r.m, r.l) : make_float2(-INFINITY, 0.0f);
+    else
+        stats[i] = r.lse2();
+}
+
 template <typename T, int D, int RS>
 __global__ __launch_bounds__(kThreads, Tune<RS>::kOcc1) void snap_pass1(
     RowView qv, RowView kv, int B, int Hkv, int N, int W, int rows, int rgroups, int nranges, int range_keys,
-    float sl2, float* __restrict__ stats) {
+    float sl2, int pair, float* __restrict__ stats) {
     constexpr int kRing = Tune<RS>::kRing1;
     constexpr int kRpg = RS * kSnapRowsPerGroup;
     using G = Geo<T, D, kRing>;
@@ -228,54 +239,82 @@ __global__ __launch_bounds__(kThreads, Tune<RS>::kOcc1) void snap_pass1(
         // the two lane halves hold the same row and different keys
         lse2_merge(rsum[rs].m, rsum[rs].l, __shfl_xor(rsum[rs].m, 32), __shfl_xor(rsum[rs].l, 32));
         if (lane < 32)
-            stats[((size_t)sp.vseg * nranges + sp.range) * kRpg + (wave * RS + rs) * 32 + lane] = rsum[rs].lse2();
+            store_stats(stats, ((size_t)sp.vseg * nranges + sp.range) * kRpg + (wave * RS + rs) * 32 + lane, pair,
+                        rsum[rs]);
     }
 }
 
-// log2 of a row's softmax denominator from its ranges' values (v0[c * pitch],
-// c < nranges): SPLIT threads per row, adjacent lanes; thread `sub` merges
-// every SPLIT-th range, 32 ranges' values loaded before any is merged, then
-// the partial sums merge by shuffles.  +inf for a row without a visible key.
+// A log-sum-exp as hi + lo (hi of its magnitude, lo below hi's last bit or of
+// the order of 1): the sum of a reference and a logarithm without the rounding
+// of either at the sum's magnitude.
+struct Lse2 {
+    float hi, lo;
+};
+__device__ __forceinline__ Lse2 lse2_of(float m, float l) {
+    // l = f 2^e, f in [1/2, 1): log2 f is rounded at its own magnitude
+    const float e = (float)__builtin_amdgcn_frexp_expf(l), f = __builtin_amdgcn_frexp_mantf(l);
+    const float s = m + e, b = s - m;
+    return {s, ((m - (s - b)) + (e - b)) + log2f(f)};  // the sum's error, exactly
+}
+
+// log2 of a row's softmax denominator from its ranges' statistics (entries
+// i0 + c pitch, c < nranges): SPLIT threads per row, adjacent lanes; thread
+// `sub` merges every SPLIT-th range, 32 ranges' values (16 pairs) loaded before
+// any is merged, then the partial sums merge by shuffles.  +inf for a row
+// without a visible key.
 template <int SPLIT>
-__device__ __forceinline__ float merge_ranges(const float* v0, int nranges, int pitch, int sub) {
+__device__ __forceinline__ Lse2 merge_ranges(const float* stats, size_t i0, bool pair, int nranges, int pitch,
+                                              int sub) {
     float a = -INFINITY, b = 0.0f;
-    for (int c0 = sub; c0 < nranges; c0 += 32 * SPLIT) {
-        float v[32];
+    if (pair) {
+        const float2* v0 = reinterpret_cast<const float2*>(stats) + i0;
+        for (int c0 = sub; c0 < nranges; c0 += 16 * SPLIT) {
+            float2 v[16];
 #pragma unroll
-        for (int j = 0; j < 32; ++j) v[j] = v0[(size_t)min(c0 + j * SPLIT, nranges - 1) * pitch];
+            for (int j = 0; j < 16; ++j) v[j] = v0[(size_t)min(c0 + j * SPLIT, nranges - 1) * pitch];
 #pragma unroll
-        for (int j = 0; j < 32; ++j)
-            if (c0 + j * SPLIT < nranges) lse2_merge(a, b, v[j], v[j] == -INFINITY ? 0.0f : 1.0f);
+            for (int j = 0; j < 16; ++j)
+                if (c0 + j * SPLIT < nranges) lse2_merge(a, b, v[j].x, v[j].y);
+        }
+    } else {
+        for (int c0 = sub; c0 < nranges; c0 += 32 * SPLIT) {
+            float v[32];
+#pragma unroll
+            for (int j = 0; j < 32; ++j) v[j] = stats[i0 + (size_t)min(c0 + j * SPLIT, nranges - 1) * pitch];
+#pragma unroll
+            for (int j = 0; j < 32; ++j)
+                if (c0 + j * SPLIT < nranges) lse2_merge(a, b, v[j], v[j] == -INFINITY ? 0.0f : 1.0f);
+        }
     }
 #pragma unroll
     for (int m = 1; m < SPLIT; m <<= 1) {
         const float ao = __shfl_xor(a, m), bo = __shfl_xor(b, m);
         lse2_merge(a, b, ao, bo);
     }
-    return b > 0.0f ? a + log2f(b) : INFINITY;
+    return b > 0.0f ? lse2_of(a, b) : Lse2{INFINITY, 0.0f};
 }
 
 // A row's log-sum-exp for pass 2 (SPLIT threads per row): merged here from
 // the ranges' values when stats is given, else as snap_combine or the import
 // step left it.  +inf for rows past the window rows.
 template <int SPLIT>
-__device__ __forceinline__ float row_lse2(const float* lse, const float* stats, int vseg, int nranges, int rpg, int r,
-                                          int sub, bool valid) {
-    if (stats == nullptr) return lse[(size_t)vseg * rpg + r];
-    const float l2 = merge_ranges<SPLIT>(stats + (size_t)vseg * nranges * rpg + r, nranges, rpg, sub);
-    return valid ? l2 : INFINITY;
+__device__ __forceinline__ Lse2 row_lse2(const float* lse, const float* stats, bool pair, int vseg, int nranges,
+                                         int rpg, int r, int sub, bool valid) {
+    if (stats == nullptr) return {lse[(size_t)vseg * rpg + r], 0.0f};
+    const Lse2 l2 = merge_ranges<SPLIT>(stats, (size_t)vseg * nranges * rpg + r, pair, nranges, rpg, sub);
+    return valid ? l2 : Lse2{INFINITY, 0.0f};
 }
 
 // Four threads per row of a row group (thread 4 r + s, rpg = blockDim.x / 4 rows).
 constexpr int kCombineSplit = 4;
 __global__ __launch_bounds__(2 * kSnapRowsPerGroup * kCombineSplit) void snap_combine(
-    const float* __restrict__ stats, int nranges, int rows, int rgroups, float* __restrict__ lse) {
+    const float* __restrict__ stats, int pair, int nranges, int rows, int rgroups, float* __restrict__ lse) {
     const int vseg = blockIdx.x, rpg = blockDim.x / kCombineSplit;
     const int r = threadIdx.x / kCombineSplit, sub = threadIdx.x % kCombineSplit;
     const int row = (vseg % rgroups) * rpg + r;
-    const float l2 = merge_ranges<kCombineSplit>(stats + (size_t)vseg * nranges * rpg + r, nranges, rpg, sub);
+    const Lse2 l2 = merge_ranges<kCombineSplit>(stats, (size_t)vseg * nranges * rpg + r, pair, nranges, rpg, sub);
     // rows past the window rows contribute nothing to the column sums
-    if (sub == 0) lse[(size_t)vseg * rpg + r] = row < rows ? l2 : INFINITY;
+    if (sub == 0) lse[(size_t)vseg * rpg + r] = row < rows ? l2.hi + l2.lo : INFINITY;
 }
 
 // Row statistics supplied by the caller (the natural-log log-sum-exp of each
@@ -295,7 +334,8 @@ __global__ __launch_bounds__(2 * kSnapRowsPerGroup) void snap_import_lse(const f
 template <typename T, int D, int RS>
 __global__ __launch_bounds__(kThreads, Tune<RS>::kOcc2) void snap_pass2(
     RowView qv, RowView kv, int B, int Hkv, int N, int W, int rows, int rgroups, int nranges, int range_keys,
-    float sl2, const float* __restrict__ lse, const float* __restrict__ stats, int segs, float* __restrict__ raw) {
+    float sl2, const float* __restrict__ lse, const float* __restrict__ stats, int pair, int segs,
+    float* __restrict__ raw) {
     constexpr int kRing = Tune<RS>::kRing2;
     constexpr int kRpg = RS * kSnapRowsPerGroup;
     using G = Geo<T, D, kRing>;
@@ -320,9 +360,11 @@ __global__ __launch_bounds__(kThreads, Tune<RS>::kOcc2) void snap_pass2(
     {
         const int r = threadIdx.x / kPerRow, sub = threadIdx.x % kPerRow;
         const int row = sp.rg * kRpg + r;
-        const float l2 = row_lse2<kPerRow>(lse, stats, sp.vseg, nranges, kRpg, r, sub, row < rows);
+        const Lse2 l2 = row_lse2<kPerRow>(lse, stats, pair, sp.vseg, nranges, kRpg, r, sub, row < rows);
         if (sub == 0) {
-            sinit[r] = -l2 / sl2;
+            // -(hi + lo) / sl2 with one rounding: the quotient, then its remainder and lo
+            const float qt = l2.hi / sl2;
+            sinit[r] = fabsf(qt) == INFINITY ? -qt : -(qt + (fmaf(-qt, sl2, l2.hi) + l2.lo) / sl2);
             swin[r] = row % W;
         }
     }
@@ -448,7 +490,11 @@ __global__ __launch_bounds__(kThreads, Tune<RS>::kOcc2) void snap_pass2(
 // as float32, each wave splits a quarter of it into the two planes the products
 // read, and the next chunk's loads go out once every wave has read the raw
 // slot, so that they are in flight beside the products.  64.5 KB of LDS at
-// d = 128: two workgroups per CU.
+// d = 128: two workgroups per CU.  A score call of one layer of 32768 keys (32
+// heads over 8, W = 32, d = 128) took 325 us with v_mfma_f32_32x32x2_f32 (one
+// workgroup per CU) and takes 98; 4 x 2 x 16384 keys 1100 and 300 us.  What is
+// left is the chain of a chunk (load, split, products, exponentials) at two
+// workgroups per CU; the two reads of K would take 40 of the 98 us.
 template <int D>
 struct SplitLds {
     using S = SplitChunk<D>;
@@ -472,7 +518,7 @@ __device__ __forceinline__ float load_q_split(typename SplitChunk<D>::Frags& qf,
 template <int D>
 __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void snap_pass1_f32(
     RowView qv, RowView kv, int B, int Hkv, int N, int W, int rows, int rgroups, int nranges, int range_keys,
-    float sl2, float* __restrict__ stats) {
+    float sl2, int pair, float* __restrict__ stats) {
     using S = SplitChunk<D>;
     __shared__ SplitLds<D> sh;
     const int lane = threadIdx.x & 63;
@@ -537,14 +583,15 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void snap_pass1_f32(
     // the two lane halves hold the same row and different keys
     lse2_merge(rsum[0].m, rsum[0].l, __shfl_xor(rsum[0].m, 32), __shfl_xor(rsum[0].l, 32));
     if (lane < 32)
-        stats[((size_t)sp.vseg * nranges + sp.range) * kSnapRowsPerGroup + wave * 32 + lane] = rsum[0].lse2();
+        store_stats(stats, ((size_t)sp.vseg * nranges + sp.range) * kSnapRowsPerGroup + wave * 32 + lane, pair,
+                    rsum[0]);
 }
 
 template <int D>
 __global__ __launch_bounds__(kThreads, 2) void snap_pass2_f32(RowView qv, RowView kv, int B, int Hkv, int N, int W,
                                                               int rows, int rgroups, int nranges, int range_keys,
                                                               float sl2, const float* __restrict__ lse,
-                                                              const float* __restrict__ stats, int segs,
+                                                              const float* __restrict__ stats, int pair, int segs,
                                                               float* __restrict__ raw) {
     using S = SplitChunk<D>;
     constexpr int kRpg = kSnapRowsPerGroup;
@@ -571,9 +618,9 @@ __global__ __launch_bounds__(kThreads, 2) void snap_pass2_f32(RowView qv, RowVie
         constexpr int kPerRow = kThreads / kRpg;
         const int r = threadIdx.x / kPerRow, sub = threadIdx.x % kPerRow;
         const int row = sp.rg * kRpg + r;
-        const float l2 = row_lse2<kPerRow>(lse, stats, sp.vseg, nranges, kRpg, r, sub, row < rows);
+        const Lse2 l2 = row_lse2<kPerRow>(lse, stats, pair, sp.vseg, nranges, kRpg, r, sub, row < rows);
         if (sub == 0) {
-            sinit[r] = -l2;
+            sinit[r] = -(l2.hi + l2.lo);
             swin[r] = row % W;
         }
     }
@@ -844,22 +891,22 @@ void launch_passes(const RowView& qv, const RowView& kv, int B, int Hkv, const f
     } else {
         if constexpr (sizeof(T) == 2)
             hipLaunchKernelGGL((snap_pass1<T, D, RS>), grid, dim3(kThreads), 0, st, qv, kv, B, Hkv, N, W, p.rows,
-                               p.rgroups, p.nranges, p.range_keys, sl2, stats);
+                               p.rgroups, p.nranges, p.range_keys, sl2, p.pair, stats);
         else
             hipLaunchKernelGGL((snap_pass1_f32<D>), grid, dim3(kThreads), 0, st, qv, kv, B, Hkv, N, W, p.rows,
-                               p.rgroups, p.nranges, p.range_keys, sl2, stats);
+                               p.rgroups, p.nranges, p.range_keys, sl2, p.pair, stats);
         merge = p.nranges <= kMergeRanges;
         if (!merge)
             hipLaunchKernelGGL(snap_combine, dim3((unsigned)p.n_vsegs), dim3(p.rpg * kCombineSplit), 0, st, stats,
-                               p.nranges, p.rows, p.rgroups, lse);
+                               p.pair, p.nranges, p.rows, p.rgroups, lse);
     }
     const float* ranges = merge ? stats : nullptr;
     if constexpr (sizeof(T) == 2)
         hipLaunchKernelGGL((snap_pass2<T, D, RS>), grid, dim3(kThreads), 0, st, qv, kv, B, Hkv, N, W, p.rows,
-                           p.rgroups, p.nranges, p.range_keys, sl2, lse, ranges, p.segs, raw);
+                           p.rgroups, p.nranges, p.range_keys, sl2, lse, ranges, p.pair, p.segs, raw);
     else
         hipLaunchKernelGGL((snap_pass2_f32<D>), grid, dim3(kThreads), 0, st, qv, kv, B, Hkv, N, W, p.rows, p.rgroups,
-                           p.nranges, p.range_keys, sl2, lse, ranges, p.segs, raw);
+                           p.nranges, p.range_keys, sl2, lse, ranges, p.pair, p.segs, raw);
 }
 
 template <typename T, int D>
