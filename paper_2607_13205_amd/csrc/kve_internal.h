@@ -33,9 +33,15 @@ inline size_t h2o_workspace(int L, int B, int Hq, int N) {
 // splits of whole kDecodeQuantum-row quanta, one workgroup each (about
 // kDecodeTargetGroups workgroups in all); each writes per head the partial
 // output o[d] and its (reference, denominator) pair, merged by a last step.
+// One workgroup per compute unit: more splits only add starts and partials to
+// merge (bf16, d = 128: 128 segments of 1639 rows take 21 us at 256 workgroups
+// and 24 at 1024, 8 of 32768 25.8 and 27.9, 2 of 20000 14.0 and 16.9; float32,
+// 32 of 5000 30.8 and 37.4; 256 of 6000 134 and 136).  The workspace is sized
+// for kDecodeSizeGroups, as it always was.
 // ---------------------------------------------------------------------------
 constexpr int kDecodeQuantum = 128;
-constexpr int kDecodeTargetGroups = 1024;  // one split per segment once there are 1024 segments
+constexpr int kDecodeTargetGroups = 256;
+constexpr int kDecodeSizeGroups = 1024;
 constexpr int kDecodeMaxGroup = 8;  // query heads per KV head
 
 struct DecodePlan {
@@ -48,13 +54,18 @@ inline DecodePlan decode_plan(int L, int B, int Hq, int Hkv, int k_cap, int d) {
     p.segs = L * B * Hkv;
     p.G = Hq / Hkv;
     const long long quanta = (k_cap + kDecodeQuantum - 1) / kDecodeQuantum;
-    long long ns = (kDecodeTargetGroups + p.segs - 1) / p.segs;
-    if (ns > quanta) ns = quanta;
-    if (ns < 1) ns = 1;
-    const long long per = (quanta + ns - 1) / ns;
+    // quanta per split and splits for a number of workgroups
+    auto splits = [&](int groups, long long& per) {
+        long long ns = (groups + p.segs - 1) / p.segs;
+        if (ns > quanta) ns = quanta;
+        if (ns < 1) ns = 1;
+        per = (quanta + ns - 1) / ns;
+        return (quanta + per - 1) / per;
+    };
+    long long per;
+    const size_t parts = (size_t)p.segs * splits(kDecodeSizeGroups, per) * p.G;
+    p.nsplit = (int)splits(kDecodeTargetGroups, per);
     p.split_keys = (int)(per * kDecodeQuantum);
-    p.nsplit = (int)((quanta + per - 1) / per);
-    const size_t parts = (size_t)p.segs * p.nsplit * p.G;
     p.off_o = 0;
     p.off_ml = align_up(parts * d * sizeof(float));
     p.total = p.off_ml + align_up(parts * 2 * sizeof(float));

@@ -1088,8 +1088,8 @@ def test_decode_matches_oracle(K, case):
     (4, 1, 128, 128, "bf16"),      # one split per segment: no merge
     (3, 1, 16 * 128, 64, "f32"),   # 16 splits: one wave per row
     (8, 1, 17 * 128, 128, "bf16"),  # 17: four waves per row, shares of 4 and 5
-    (6, 2, 80 * 128 + 5, 64, "bf16"),
-    (2, 1, 300 * 128, 128, "f32")])  # shares of 75: more than one 64-split step per wave
+    (6, 2, 80 * 128 + 5, 64, "bf16"),  # splits of two quanta, the last of 5 rows
+    (2, 1, 300 * 128, 128, "f32")])  # 100 splits of three quanta
 def test_decode_merge_of_many_splits(K, Hq, Hkv, k_cap, d, dt):
     """The merge of the splits at the edges of its forms, with empty splits
     past a short count."""
