@@ -166,7 +166,7 @@ __global__ __launch_bounds__(kThreads, 2) void h2o_pass1_x2(RowView qv, RowView 
     const int t_end = min(N, p0 + npos);  // keys up to the block's last position
     const int nch = (t_end + kKeys - 1) / kKeys;
     typename G::Rd rd;
-    rd.init(lane, 0);
+    rd.init(lane);
     typename G::Ring ring_io;
     ring_io.open(nch, wave, lane, (unsigned)kv.s_token);
     const RowChunks<T, D> src{head_rows(kv, lb, B, j), kv.s_token, 0, t_end};
@@ -464,7 +464,7 @@ __global__ __launch_bounds__(kThreads, 2) void h2o_pass2_x2(RowView qv, RowView 
     // rows kb0 .. N - 1 of this head
     const int nch = (N - kb0 + kKeys - 1) / kKeys;
     typename G::Rd rd;
-    rd.init(lane, 0);
+    rd.init(lane);
     typename G::Wr wr;
     wr.init(wave, lane, (unsigned)qv.s_token);
     // chunk c: rows from kb0 + 64 c, with their 64 start values, as in

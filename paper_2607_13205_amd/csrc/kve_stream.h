@@ -62,39 +62,26 @@ __device__ __forceinline__ void lds_dma16(const char* base, unsigned voff, const
                      :: "v"(voff), "s"(base), "{m0}"(m0) : "memory");
 }
 
-// Matrix-core fragments of a chunk, read from LDS with per-lane byte offsets
-// worked out once per kernel.  Fragment (kb, st) of lane l is key row
-// 32 kb + l%32 (counted from the wave's first key row, `base` bytes into the
-// chunk) at k-step st.  With bf16 the swizzled offset of each k-step is
-// kept in a register (k-step st reads piece 2 st + lane / 32), so that a read
-// is one ds_read_b128 whose slot and key-block parts are immediate offsets;
-// fp32 chunks (D/2 k-steps) work the offset out at each read.
+// Matrix-core fragments of a chunk of 16-bit rows, read from LDS with per-lane
+// byte offsets worked out once per kernel.  Fragment (kb, st) of lane l is key
+// row 32 kb + l%32 at k-step st (piece 2 st + l / 32): one ds_read_b128 whose
+// slot and key-block parts are immediate offsets.
 template <typename T, int D, int KEYS>
 struct ChunkReader {
     using C = KChunk<T, D, KEYS>;
     using M = Mma<T>;
-    static constexpr bool kTable = sizeof(T) == 2;
-    static constexpr int NOFF = kTable ? C::NSTEP : 1;
-    int off[NOFF];
-    int lane, base;
+    static_assert(sizeof(T) == 2, "one 16-byte piece per fragment");
+    int off[C::NSTEP];
 
-    __device__ __forceinline__ void init(int lane_, int base_) {
-        lane = lane_;
-        base = base_;
-        if constexpr (kTable) {
+    __device__ __forceinline__ void init(int lane) {
 #pragma unroll
-            for (int st = 0; st < NOFF; ++st) off[st] = offset(st);
+        for (int st = 0; st < C::NSTEP; ++st) {
+            const int byte = (st * M::KSTEP + (lane >> 5) * M::KPL) * C::ES;
+            off[st] = chunk_swz<C::ROW>(lane & 31, byte >> 4) + (byte & 15);
         }
     }
-    __device__ __forceinline__ int offset(int st) const {
-        const int byte = (st * M::KSTEP + (lane >> 5) * M::KPL) * C::ES;
-        return base + chunk_swz<C::ROW>(lane & 31, byte >> 4) + (byte & 15);
-    }
     __device__ __forceinline__ typename M::frag get(const char* slot, int kb, int st) const {
-        if constexpr (kTable)
-            return M::load(slot + kb * 32 * C::ROW + off[st], 0);
-        else
-            return M::load(slot + kb * 32 * C::ROW + offset(st), 0);
+        return M::load(slot + kb * 32 * C::ROW + off[st], 0);
     }
 };
 
@@ -249,68 +236,16 @@ struct ChunkRing {
     }
 };
 
-// Products of one chunk's first 64 rows (two 32-row blocks b, fragments from
-// LDS) with 32 rows held in registers (reg[st]).  LDS_A: the chunk rows are the
-// A operand (element i of acc[b] belongs to chunk row 32 b + c_row(i, lane),
-// the lane to register row lane % 32); otherwise the register rows are
-// (element i belongs to register row c_row(i, lane) in both blocks, the lane
-// to chunk row 32 b + lane % 32).  acc[b] starts at zero or, given `init`, at
-// the init value of the A-operand row of each element: init[32 b + c_row(i)]
-// with LDS_A, init[c_row(i)] otherwise (rows c_row(4 a .. 4 a + 3) are four
-// consecutive floats).
-//
-// c_init, when given, replaces `init`: acc[b] starts at c_init[LDS_A ? b : 0]
-// (values already in registers).
-template <typename T, int D, int KEYS, bool LDS_A>
-__device__ __forceinline__ void chunk_mma(f32x16 (&acc)[2], const ChunkReader<T, D, KEYS>& rd, const char* slot,
-                                          const typename Mma<T>::frag (&reg)[KChunk<T, D, KEYS>::NSTEP],
-                                          const float* init, int lane, const f32x16* c_init = nullptr) {
-    using M = Mma<T>;
-    constexpr int NS = KChunk<T, D, KEYS>::NSTEP;
-    f32x16 c0[2];
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-        if (c_init != nullptr) {
-            c0[b] = c_init[LDS_A ? b : 0];
-        } else if (init == nullptr) {
-            c0[b] = f32x16{};
-        } else {
-#pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                const float4 v = *reinterpret_cast<const float4*>(init + (LDS_A ? 32 * b : 0) + c_row(4 * a, lane));
-                c0[b][4 * a] = v.x;
-                c0[b][4 * a + 1] = v.y;
-                c0[b][4 * a + 2] = v.z;
-                c0[b][4 * a + 3] = v.w;
-            }
-        }
-    }
-#pragma unroll
-    for (int st = 0; st < NS; ++st) {
-        const typename M::frag f[2] = {rd.get(slot, 0, st), rd.get(slot, 1, st)};
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const f32x16 c = st == 0 ? c0[b] : acc[b];
-            acc[b] = LDS_A ? M::mma(f[b], reg[st], c) : M::mma(reg[st], f[b], c);
-        }
-    }
-    if constexpr (ChunkReader<T, D, KEYS>::kTable) {
-        // keep the fragment reads two k-steps ahead of the products
-        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);  // LDS reads of steps 0, 1
-#pragma unroll
-        for (int st = 0; st < NS; ++st) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);  // products of step st
-            if (st + 2 < NS) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);  // reads of step st + 2
-        }
-    }
-}
-
-// chunk_mma for RS sets of 32 register rows at once: acc[s][b] is register set
-// s against chunk block b, in the layout chunk_mma gives for one set.  Each
-// fragment read from LDS feeds RS products and the 2 RS accumulators are
-// independent chains.  The products start from acc itself with acc_init (the
-// caller filled it), else from c_init, when given (the start value of each
-// set: register rows, !LDS_A), else from zero.
+// Products of one chunk's 64 rows (two 32-row blocks b, fragments from LDS)
+// with RS sets of 32 rows held in registers (reg[s][st]).  LDS_A: the chunk
+// rows are the A operand (element i of acc[s][b] belongs to chunk row 32 b +
+// c_row(i, lane), the lane to register row lane % 32 of set s); otherwise the
+// register rows are (element i belongs to register row c_row(i, lane), the
+// lane to chunk row 32 b + lane % 32).  Each fragment read from LDS feeds RS
+// products and the 2 RS accumulators are independent chains.  The products
+// start from acc itself with acc_init (the caller filled it), else from
+// c_init, when given (the start value of each set: register rows, !LDS_A),
+// else from zero.
 template <typename T, int D, int KEYS, bool LDS_A, int RS>
 __device__ __forceinline__ void chunk_mma_sets(f32x16 (&acc)[RS][2], const ChunkReader<T, D, KEYS>& rd,
                                                const char* slot,
@@ -329,14 +264,12 @@ __device__ __forceinline__ void chunk_mma_sets(f32x16 (&acc)[RS][2], const Chunk
                 acc[rs][b] = LDS_A ? M::mma(f[b], reg[rs][st], c) : M::mma(reg[rs][st], f[b], c);
             }
     }
-    if constexpr (ChunkReader<T, D, KEYS>::kTable) {
-        // keep the fragment reads two k-steps ahead of the products
-        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);  // LDS reads of steps 0, 1
+    // keep the fragment reads two k-steps ahead of the products
+    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);  // LDS reads of steps 0, 1
 #pragma unroll
-        for (int st = 0; st < NS; ++st) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 2 * RS, 0);  // products of step st
-            if (st + 2 < NS) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);  // reads of step st + 2
-        }
+    for (int st = 0; st < NS; ++st) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 2 * RS, 0);  // products of step st
+        if (st + 2 < NS) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);  // reads of step st + 2
     }
 }
 
@@ -380,14 +313,6 @@ struct RowSum {
         l = a;
         m = mn;
     }
-    __device__ __forceinline__ void add(const f32x16 (&x)[2], float sl2) {
-        const float ln = l + part(x, sl2);
-        if (ln <= 0x1p64f) {  // false for inf and NaN
-            l = ln;
-            return;
-        }
-        reset(x, sl2);
-    }
     // log2 of the sum, -inf when empty
     __device__ __forceinline__ float lse2() const { return (m != -INFINITY && l > 0.0f) ? m + log2f(l) : -INFINITY; }
 };
@@ -406,7 +331,7 @@ __device__ __forceinline__ void interleave_trans() {
     }
 }
 
-// RowSum::add for RS sets at once: the exponentials and sums of every set in
+// A chunk's logits x added to RS sets' sums: the exponentials and sums of every set in
 // one block (one wave's vector work per chunk), then one test of all sums.
 template <int RS>
 __device__ __forceinline__ void row_sums_add(RowSum (&r)[RS], const f32x16 (&x)[RS][2], float sl2) {

@@ -187,7 +187,7 @@ __global__ __launch_bounds__(kThreads, Tune<RS>::kOcc1) void snap_pass1(
 #pragma unroll
     for (int rs = 0; rs < RS; ++rs) load_q<T, D>(qf[rs], qseg, qv, rows, W, qrow(rs), lane);
     typename G::Rd rd;
-    rd.init(lane, 0);
+    rd.init(lane);
     typename G::Ring ring_io;
     ring_io.open(sp.nch, wave, lane, (unsigned)kv.s_token);
     const KeyChunks<T, D> src{seg_rows(kv, sp.seg, B, Hkv, 1), kv.s_token, sp.t_begin, sp.t_end};
@@ -397,7 +397,7 @@ __global__ __launch_bounds__(kThreads, Tune<RS>::kOcc2) void snap_pass2(
         }
     }
     typename G::Rd rd;
-    rd.init(lane, 0);
+    rd.init(lane);
     typename G::Ring ring_io;
     ring_io.open(sp.nch, wave, lane, (unsigned)kv.s_token);
     const KeyChunks<T, D> src{seg_rows(kv, sp.seg, B, Hkv, 1), kv.s_token, sp.t_begin, sp.t_end};
