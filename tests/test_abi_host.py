@@ -260,3 +260,28 @@ def test_snapkv_rejects_more_window_rows_than_supported_before_any_launch(kve):
     # W = 64: 1024 rows, accepted by the row check, refused for the 16-byte workspace
     st = lib.kve_snapkv_score(fake, fake, 0, 1, 1, 16, 1, 4096, 64, 128, 0.0, 7, score, ws, 16, None)
     assert st == kve.binding.KVE_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("L,B,Hq,Hkv,N,W,d", [(1, 1, 2, 1, 512, 16, 64), (1, 1, 32, 8, 8192, 32, 128),
+                                              (8, 2, 32, 8, 20011, 32, 128), (1, 1, 32, 8, 131072, 64, 128),
+                                              (32, 4, 32, 8, 32768, 32, 128), (2, 3, 12, 3, 5003, 50, 64)])
+def test_workspace_sizes_do_not_follow_the_launch_rules(kve, L, B, Hq, Hkv, N, W, d):
+    """The sizes are those of the smallest key ranges (score) and of 1024
+    workgroups (decode), whatever a call's own plan takes."""
+    def up(x):
+        return (x + 255) // 256 * 256
+    segs, rows, chunks = L * B * Hkv, Hq // Hkv * W, -(-N // 64)
+
+    def score(elem):
+        rpg = 256 if elem == 2 and rows > 128 else 128
+        groups = -(-rows // rpg)
+        per = -(-chunks * segs * groups // 4096)
+        per = min(max(per, -(-min(rows, rpg) // 64)), 128, chunks)
+        ranges = -(-chunks // per)
+        return up(4 * segs * groups * ranges * rpg) + up(4 * segs * groups * rpg) + up(4 * groups * segs * N)
+    assert kve.snapkv_workspace_size(L, B, Hq, Hkv, N, W, d) == max(score(2), score(4))
+    assert kve.topk_workspace_size(L, B, Hkv, N, 4) == up(8 * segs * N)
+    quanta = -(-N // 128)
+    per = -(-quanta // max(1, min(quanta, -(-1024 // segs))))
+    parts = segs * -(-quanta // per) * (Hq // Hkv)
+    assert kve.decode_workspace_size(L, B, Hq, Hkv, N, d) == up(4 * parts * d) + up(8 * parts)
