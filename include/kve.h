@@ -109,7 +109,11 @@ size_t kve_snapkv_workspace_size(int L, int B, int Hq, int Hkv, int N, int W, in
  *   score  [L, B, Hkv, N] float32 output (device)
  *
  * Requires 1 <= W <= N, G*W <= 1024.  Scores are accumulated in float32 from
- * products of the input type; each row's softmax is taken relative to a
+ * products of the input type.  Float32 rows whose elements span few enough
+ * binades are multiplied as pairs of float16 rows (an error of up to 8 units of
+ * 2^-24 of sum |q| |k| per logit beside that of the sums, and 2^-22 / log2(e)
+ * at most from elements far below their row's largest); other rows, and rows
+ * with infinite elements, as float32.  Each row's softmax is taken relative to a
  * running reference that is raised to the largest logit seen whenever a
  * partial sum would leave [0, 2^64], so no exponential overflows and the
  * per-chunk sums merge exactly.

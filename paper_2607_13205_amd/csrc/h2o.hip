@@ -215,15 +215,17 @@ __global__ __launch_bounds__(kThreads, 2) void h2o_pass1_x2(RowView qv, RowView 
 // products and the exponentials, like the bf16 passes: 32 query heads, N =
 // 16003, d = 128 take 5.99 ms (1.05 PFLOP/s of 16-bit products) against 15.45
 // ms with v_mfma_f32_32x32x2_f32 (0.14 PFLOP/s, 87% of that instruction's
-// rate); the scores are 2.9e-7 off their 64-bit values with either.
+// rate); the scores are 2.9e-7 off their 64-bit values with either.  Rows that
+// pairs do not hold (one channel of the keys 2^20 times the others) go through
+// the float32 instruction after all: 16.7 ms.
+// The lane as the split and the products take it.  d = 128: addresses worked out
+// of it are not kept across the chunk loop, where the fragments leave no
+// registers for them: a spilled one comes back by a load that waits for the
+// chunk loads in flight (16003 rows, 32 heads: 6.1 ms, 5.7 without).
 template <int D>
-struct SplitLds {
-    using S = SplitChunk<D>;
-    __align__(16) char raw[S::Raw::BYTES];
-    __align__(16) char hi[S::PLANE];
-    __align__(16) char lo[S::PLANE];
-    __align__(16) float unscale[kKeys];
-};
+__device__ __forceinline__ int fresh_lane(int lane) {
+    return D == 128 ? SplitChunk<D>::opaque(lane) : lane;
+}
 
 // acc (scaled products) times the scales of its chunk row and register row
 template <int RS>
@@ -249,7 +251,7 @@ __global__ __launch_bounds__(kThreads, 2) void h2o_pass1_f32(RowView qv, RowView
                                                              int NP, int npos, int nblk, float sl2,
                                                              float* __restrict__ linit) {
     using S = SplitChunk<D>;
-    __shared__ SplitLds<D> sh;
+    __shared__ typename S::Lds sh;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int Gh = Hq / Hkv;
@@ -263,28 +265,32 @@ __global__ __launch_bounds__(kThreads, 2) void h2o_pass1_f32(RowView qv, RowView
     int lim[2];  // last key the row sees (-1: no row)
     typename S::Frags qf[2];
     float ls[2];  // scale of this lane's rows, times sl2
+    RowMag mag[2];
+    auto qrow = [&](int rs, int ln) {
+        const int r = wave * 64 + rs * 32 + (ln & 31);
+        return head_rows(qv, lb, B, j * Gh + r % Gh) + (long long)max(lim[rs], 0) * qv.s_token;
+    };
 #pragma unroll
     for (int rs = 0; rs < 2; ++rs) {
         const int r = wave * 64 + rs * 32 + (lane & 31);
         const int pos = p0 + r / Gh;
-        const bool valid = r < npos * Gh && pos < N;
-        ls[rs] = sl2 * S::load_row(qf[rs],
-                                   head_rows(qv, lb, B, j * Gh + r % Gh) + (long long)(valid ? pos : 0) * qv.s_token,
-                                   valid, lane);
-        lim[rs] = valid ? pos : -1;
+        lim[rs] = r < npos * Gh && pos < N ? pos : -1;
+        ls[rs] = sl2 * S::load_row(qf[rs], mag[rs], qrow(rs, lane), lim[rs] >= 0, lane);
     }
     const int t_end = min(N, p0 + npos);  // keys up to the block's last position
     const int nch = (t_end + kKeys - 1) / kKeys;
     typename Geo<float, D>::Wr wr;
     wr.init(wave, lane, (unsigned)kv.s_token);
     const char* kbase = head_rows(kv, lb, B, j);
-    auto issue = [&](int c) { wr.issue(sh.raw, kbase + (long long)(c * kKeys) * kv.s_token, t_end - c * kKeys); };
-    issue(0);
+    auto issue = [&](int c, char* slot) {
+        wr.issue(slot, kbase + (long long)(c * kKeys) * kv.s_token, t_end - c * kKeys);
+    };
+    issue(0, sh.raw);
+    const RowMag gmag = S::group_mag(sh, mag, ls, sl2, wave, lane);
+    auto own_lane = [&] { return fresh_lane<D>(lane); };
 
-    RowSum rsum[2];
-    auto logits = [&](f32x16 (&acc)[2][2], int s) {
-        S::template mma<true, 2>(acc, sh.hi, sh.lo, qf, lane);
-        unscale_acc<2>(acc, sh.unscale, ls, lane);
+    RowSum rsum[2], kept[2];
+    auto mask = [&](f32x16 (&acc)[2][2], int s) {
         if ((s + 1) * kKeys > p0) {  // a key of the chunk lies after some row of the block
 #pragma unroll
             for (int rs = 0; rs < 2; ++rs) {
@@ -298,13 +304,16 @@ __global__ __launch_bounds__(kThreads, 2) void h2o_pass1_f32(RowView qv, RowView
             }
         }
     };
+    int s = 0;
 #pragma unroll 1
-    for (int s = 0; s < nch; ++s) {
-        wait_vmcnt<0>();
-        lds_barrier();  // chunk s landed; every wave is done with the planes of chunk s - 1
-        S::convert(sh.raw, sh.hi, sh.lo, sh.unscale, wave, lane);
+    for (; s < nch; ++s) {
+        if (s > 0) {
+            wait_vmcnt<0>();
+            lds_barrier();  // chunk s landed; every wave is done with the planes of chunk s - 1
+        }
+        S::convert(sh, gmag, wave, own_lane());
         lds_barrier();  // planes written, raw slot read
-        if (s + 1 < nch) issue(s + 1);
+        if (s + 1 < nch) issue(s + 1, sh.raw);
         // a second round, of the whole wave, when a sum left [0, 2^64]: the
         // exponentials replaced the logits, and the planes stay until the next
         // barrier
@@ -312,13 +321,41 @@ __global__ __launch_bounds__(kThreads, 2) void h2o_pass1_f32(RowView qv, RowView
 #pragma unroll 1
         for (bool again = false;; again = true) {
             f32x16 acc[2][2];
-            logits(acc, s);
+            S::template mma<true, 2>(acc, sh, qf, own_lane());
+            unscale_acc<2>(acc, sh.unscale, ls, lane);
+            mask(acc, s);
             if (again) {
                 row_sums_fix<2>(rsum, acc, 1.0f, ln);
                 break;
             }
             if (row_sums_try<2>(rsum, acc, 1.0f, ln)) break;
         }
+        if (S::check(s, nch)) {
+            if (S::wide(sh)) break;
+            kept[0] = rsum[0];
+            kept[1] = rsum[1];
+        }
+    }
+    if (s < nch) {  // some row was too wide
+        rsum[0] = kept[0];
+        rsum[1] = kept[1];
+        typename S::FragsF32 qw[2];
+#pragma unroll
+        for (int rs = 0; rs < 2; ++rs) S::load_row_f32(qw[rs], qrow(rs, S::opaque(lane)), lim[rs] >= 0, lane);
+        S::rest_f32(sh, s / S::kCheck * S::kCheck, nch, issue, [&](int c, const char* slot) {
+            float ln[2];
+#pragma unroll 1
+            for (bool again = false;; again = true) {
+                f32x16 acc[2][2];
+                S::template mma_f32<true, 2>(acc, slot, qw, lane);
+                mask(acc, c);
+                if (again) {
+                    row_sums_fix<2>(rsum, acc, sl2, ln);
+                    break;
+                }
+                if (row_sums_try<2>(rsum, acc, sl2, ln)) break;
+            }
+        });
     }
 #pragma unroll
     for (int rs = 0; rs < 2; ++rs) {
@@ -338,7 +375,7 @@ __global__ __launch_bounds__(kThreads, 2) void h2o_pass2_f32(RowView qv, RowView
                                                              float* __restrict__ colsum) {
     using S = SplitChunk<D>;
     constexpr int kBlock = 2 * kKeyBlock;
-    __shared__ SplitLds<D> sh;
+    __shared__ typename S::Lds sh;
     __shared__ __align__(16) float sli[2][kKeys];  // -lse2 of each chunk row
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -350,13 +387,15 @@ __global__ __launch_bounds__(kThreads, 2) void h2o_pass2_f32(RowView qv, RowView
     int key[2];
     typename S::Frags kf[2];
     float ls[2];  // scale of this lane's keys, times sl2
+    RowMag mag[2];
+    auto krow = [&](int ks) {
+        return head_rows(kv, (int)(lbj / Hkv), B, (int)(lbj % Hkv)) +
+               (long long)(key[ks] < N ? key[ks] : 0) * kv.s_token;
+    };
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
         key[ks] = kb0 + wave * 64 + ks * 32 + (lane & 31);
-        ls[ks] = sl2 * S::load_row(kf[ks],
-                                   head_rows(kv, (int)(lbj / Hkv), B, (int)(lbj % Hkv)) +
-                                       (long long)(key[ks] < N ? key[ks] : 0) * kv.s_token,
-                                   key[ks] < N, lane);
+        ls[ks] = sl2 * S::load_row(kf[ks], mag[ks], krow(ks), key[ks] < N, lane);
     }
     const char* qhead = head_rows(qv, (int)(head / Hq), B, (int)(head % Hq));
     // rows kb0 .. N - 1 of this head
@@ -367,42 +406,19 @@ __global__ __launch_bounds__(kThreads, 2) void h2o_pass2_f32(RowView qv, RowView
     // four 16-byte pieces per wave, lanes 0..3).  r0 is a multiple of 64 below
     // N, so the 64 values lie inside the head's row of pitch NP and start
     // 256-byte aligned; rows past N are masked.
-    auto issue = [&](int c) {
+    auto issue = [&](int c, char* slot) {
         const int r0 = kb0 + c * kKeys;
-        wr.issue(sh.raw, qhead + (long long)r0 * qv.s_token, N - r0);
+        wr.issue(slot, qhead + (long long)r0 * qv.s_token, N - r0);
         if (lane < 4)
             lds_dma16(reinterpret_cast<const char*>(linit + head * NP + r0), (unsigned)(wave * 64 + lane * 16),
                       reinterpret_cast<const char*>(&sli[c & 1][wave * 16]));
     };
-    issue(0);
+    issue(0, sh.raw);
+    const RowMag gmag = S::group_mag(sh, mag, ls, sl2, wave, lane);
+    auto own_lane = [&] { return fresh_lane<D>(lane); };
 
-    float col[2] = {0.0f, 0.0f};
-#pragma unroll 1
-    for (int s = 0; s < nch; ++s) {
-        wait_vmcnt<0>();
-        lds_barrier();  // chunk s landed; every wave is done with the planes of chunk s - 1
-        S::convert(sh.raw, sh.hi, sh.lo, sh.unscale, wave, lane);
-        lds_barrier();  // planes written, raw slot read
-        if (s + 1 < nch) issue(s + 1);
-        f32x16 acc[2][2];
-        S::template mma<true, 2>(acc, sh.hi, sh.lo, kf, lane);
-        // x - lse2 = acc * scales + linit of the row
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            __builtin_amdgcn_sched_barrier(0);  // one block's scales and start values in registers at a time
-#pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                const int o = 32 * b + c_row(4 * a, lane);
-                const float4 v = *reinterpret_cast<const float4*>(sh.unscale + o);
-                const float4 w = *reinterpret_cast<const float4*>(&sli[s & 1][o]);
-                const float u[4] = {v.x, v.y, v.z, v.w}, c[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-                for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        acc[ks][b][4 * a + e] = fmaf(acc[ks][b][4 * a + e], u[e] * ls[ks], c[e]);
-            }
-        }
+    float col[2] = {0.0f, 0.0f}, kept[2] = {0.0f, 0.0f};
+    auto sums = [&](f32x16 (&acc)[2][2], int s) {
         const int r0 = kb0 + s * kKeys;
         if (r0 < kb0 + kBlock || r0 + kKeys > N) {  // rows before some key, or past N
 #pragma unroll
@@ -422,6 +438,66 @@ __global__ __launch_bounds__(kThreads, 2) void h2o_pass2_f32(RowView qv, RowView
         }
         col[0] += exp2_sum(acc[0], 1.0f);
         col[1] += exp2_sum(acc[1], 1.0f);
+    };
+    int s = 0;
+#pragma unroll 1
+    for (; s < nch; ++s) {
+        if (s > 0) {
+            wait_vmcnt<0>();
+            lds_barrier();  // chunk s landed; every wave is done with the planes of chunk s - 1
+        }
+        S::convert(sh, gmag, wave, own_lane());
+        lds_barrier();  // planes written, raw slot read
+        if (s + 1 < nch) issue(s + 1, sh.raw);
+        f32x16 acc[2][2];
+        S::template mma<true, 2>(acc, sh, kf, own_lane());
+        // x - lse2 = acc * scales + linit of the row
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            __builtin_amdgcn_sched_barrier(0);  // one block's scales and start values in registers at a time
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                const int o = 32 * b + c_row(4 * a, lane);
+                const float4 v = *reinterpret_cast<const float4*>(sh.unscale + o);
+                const float4 w = *reinterpret_cast<const float4*>(&sli[s & 1][o]);
+                const float u[4] = {v.x, v.y, v.z, v.w}, c[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        acc[ks][b][4 * a + e] = fmaf(acc[ks][b][4 * a + e], u[e] * ls[ks], c[e]);
+            }
+        }
+        sums(acc, s);
+        if (S::check(s, nch)) {
+            if (S::wide(sh)) break;
+            kept[0] = col[0];
+            kept[1] = col[1];
+        }
+    }
+    if (s < nch) {  // some row was too wide
+        col[0] = kept[0];
+        col[1] = kept[1];
+        typename S::FragsF32 kw[2];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) S::load_row_f32(kw[ks], krow(ks), key[ks] < N, lane);
+        S::rest_f32(sh, s / S::kCheck * S::kCheck, nch, issue, [&](int c, const char* slot) {
+            f32x16 acc[2][2];
+            S::template mma_f32<true, 2>(acc, slot, kw, lane);
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {
+                    const float4 w = *reinterpret_cast<const float4*>(&sli[c & 1][32 * b + c_row(4 * a, lane)]);
+                    const float st[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+                    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            acc[ks][b][4 * a + e] = fmaf(acc[ks][b][4 * a + e], sl2, st[e]);
+                }
+            sums(acc, c);
+        });
     }
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {

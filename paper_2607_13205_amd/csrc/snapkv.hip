@@ -494,25 +494,15 @@ __global__ __launch_bounds__(kThreads, Tune<RS>::kOcc2) void snap_pass2(
 // heads over 8, W = 32, d = 128) took 325 us with v_mfma_f32_32x32x2_f32 (one
 // workgroup per CU) and takes 98; 4 x 2 x 16384 keys 1100 and 300 us.  What is
 // left is the chain of a chunk (load, split, products, exponentials) at two
-// workgroups per CU; the two reads of K would take 40 of the 98 us.
-template <int D>
-struct SplitLds {
-    using S = SplitChunk<D>;
-    __align__(16) char raw[S::Raw::BYTES];
-    __align__(16) char hi[S::PLANE];
-    __align__(16) char lo[S::PLANE];
-    __align__(16) float unscale[kKeys];
-};
+// workgroups per CU; the two reads of K would take 40 of the 98 us.  With rows
+// that pairs do not hold (kve_split.h): 250 us.
 template <int D>
 using SplitWr = ChunkWriter<float, D, kKeys, kWaves, true>;
 
-// Fragments of this lane's query row (zero past the window rows); returns its unscale.
-template <int D>
-__device__ __forceinline__ float load_q_split(typename SplitChunk<D>::Frags& qf, const char* qseg, const RowView& qv,
-                                              int rows, int W, int row, int lane) {
+// Window row `row` of a segment whose queries start at qseg (row 0 past its rows).
+__device__ __forceinline__ const char* q_row(const char* qseg, const RowView& qv, int rows, int W, int row) {
     const int r = row < rows ? row : 0;
-    return SplitChunk<D>::load_row(qf, qseg + (long long)(r / W) * qv.s_head + (long long)(r % W) * qv.s_token,
-                                   row < rows, lane);
+    return qseg + (long long)(r / W) * qv.s_head + (long long)(r % W) * qv.s_token;
 }
 
 template <int D>
@@ -520,7 +510,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void snap_pass1_f32(
     RowView qv, RowView kv, int B, int Hkv, int N, int W, int rows, int rgroups, int nranges, int range_keys,
     float sl2, int pair, float* __restrict__ stats) {
     using S = SplitChunk<D>;
-    __shared__ SplitLds<D> sh;
+    __shared__ typename S::Lds sh;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const Span sp = span_of(nranges, rgroups, range_keys, N);
@@ -528,26 +518,42 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void snap_pass1_f32(
     const KeyChunks<float, D> src{seg_rows(kv, sp.seg, B, Hkv, 1), kv.s_token, sp.t_begin, sp.t_end};
     SplitWr<D> wr;
     wr.init(wave, lane, (unsigned)kv.s_token);
-    auto issue = [&](int c) {
+    auto issue = [&](int c, char* slot) {
         const char* rws;
         int valid;
         src(c, &rws, &valid);
-        wr.issue(sh.raw, rws, valid);
+        wr.issue(slot, rws, valid);
     };
-    issue(0);
+    issue(0, sh.raw);
     const int qr = sp.rg * kSnapRowsPerGroup + wave * 32 + (lane & 31);  // this lane's query row
+    const char* qseg = seg_rows(qv, sp.seg, B, Hkv, rows / W);
     typename S::Frags qf[1];
-    const float ls = sl2 * load_q_split<D>(qf[0], seg_rows(qv, sp.seg, B, Hkv, rows / W), qv, rows, W, qr, lane);
+    RowMag mag[1];
+    const float ls[1] = {sl2 * S::load_row(qf[0], mag[0], q_row(qseg, qv, rows, W, qr), qr < rows, lane)};
     const int lim = qr < rows ? P_rows + qr % W : -1;  // last key the row sees
+    const RowMag gmag = S::group_mag(sh, mag, ls, sl2, wave, lane);
 
-    RowSum rsum[1];
+    RowSum rsum[1], kept[1];
+    auto mask = [&](f32x16 (&acc)[1][2], int s) {
+        if (sp.t_begin + (s + 1) * kKeys > min(P_rows, sp.t_end)) {  // past the range end or inside the window
+            const int last = min(lim, sp.t_end - 1) - (sp.t_begin + s * kKeys + 4 * (lane >> 5));
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    acc[0][kb][i] = mask_neg(acc[0][kb][i], last - (32 * kb + 8 * (i >> 2) + (i & 3)));
+        }
+    };
+    int s = 0;
 #pragma unroll 1
-    for (int s = 0; s < sp.nch; ++s) {
-        wait_vmcnt<0>();
-        lds_barrier();  // chunk s landed; every wave is done with the planes of chunk s - 1
-        S::convert(sh.raw, sh.hi, sh.lo, sh.unscale, wave, lane);
+    for (; s < sp.nch; ++s) {
+        if (s > 0) {
+            wait_vmcnt<0>();
+            lds_barrier();  // chunk s landed; every wave is done with the planes of chunk s - 1
+        }
+        S::convert(sh, gmag, wave, lane);
         lds_barrier();  // planes written, raw slot read
-        if (s + 1 < sp.nch) issue(s + 1);
+        if (s + 1 < sp.nch) issue(s + 1, sh.raw);
         float ln[1];
         // a second round, of the whole wave, when a sum left [0, 2^64]: the
         // exponentials replaced the logits, and the planes stay until the next
@@ -555,7 +561,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void snap_pass1_f32(
 #pragma unroll 1
         for (bool again = false;; again = true) {
             f32x16 acc[1][2];
-            S::template mma<true, 1>(acc, sh.hi, sh.lo, qf, lane);
+            S::template mma<true, 1>(acc, sh, qf, lane);
 #pragma unroll
             for (int b = 0; b < 2; ++b)
 #pragma unroll
@@ -563,22 +569,38 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void snap_pass1_f32(
                     const float4 v = *reinterpret_cast<const float4*>(sh.unscale + 32 * b + c_row(4 * a, lane));
                     const float u[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[0][b][4 * a + e] *= u[e] * ls;
+                    for (int e = 0; e < 4; ++e) acc[0][b][4 * a + e] *= u[e] * ls[0];
                 }
-            if (sp.t_begin + (s + 1) * kKeys > min(P_rows, sp.t_end)) {  // past the range end or inside the window
-                const int last = min(lim, sp.t_end - 1) - (sp.t_begin + s * kKeys + 4 * (lane >> 5));
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i)
-                        acc[0][kb][i] = mask_neg(acc[0][kb][i], last - (32 * kb + 8 * (i >> 2) + (i & 3)));
-            }
+            mask(acc, s);
             if (again) {
                 row_sums_fix<1>(rsum, acc, 1.0f, ln);
                 break;
             }
             if (row_sums_try<1>(rsum, acc, 1.0f, ln)) break;
         }
+        if (S::check(s, sp.nch)) {
+            if (S::wide(sh)) break;
+            kept[0] = rsum[0];
+        }
+    }
+    if (s < sp.nch) {  // some row was too wide
+        rsum[0] = kept[0];
+        typename S::FragsF32 qw[1];
+        S::load_row_f32(qw[0], q_row(qseg, qv, rows, W, qr), qr < rows, lane);
+        S::rest_f32(sh, s / S::kCheck * S::kCheck, sp.nch, issue, [&](int c, const char* slot) {
+            float ln[1];
+#pragma unroll 1
+            for (bool again = false;; again = true) {
+                f32x16 acc[1][2];
+                S::template mma_f32<true, 1>(acc, slot, qw, lane);
+                mask(acc, c);
+                if (again) {
+                    row_sums_fix<1>(rsum, acc, sl2, ln);
+                    break;
+                }
+                if (row_sums_try<1>(rsum, acc, sl2, ln)) break;
+            }
+        });
     }
     // the two lane halves hold the same row and different keys
     lse2_merge(rsum[0].m, rsum[0].l, __shfl_xor(rsum[0].m, 32), __shfl_xor(rsum[0].l, 32));
@@ -595,7 +617,7 @@ __global__ __launch_bounds__(kThreads, 2) void snap_pass2_f32(RowView qv, RowVie
                                                               float* __restrict__ raw) {
     using S = SplitChunk<D>;
     constexpr int kRpg = kSnapRowsPerGroup;
-    __shared__ SplitLds<D> sh;
+    __shared__ typename S::Lds sh;
     __shared__ __align__(16) float scol[2][kKeys][kWaves];  // column sums per key and wave, two chunks
     __shared__ __align__(16) float sinit[kRpg];             // -lse2 of each row
     __shared__ __align__(16) float srow[kRpg];              // unscale of each row, times sl2
@@ -607,13 +629,13 @@ __global__ __launch_bounds__(kThreads, 2) void snap_pass2_f32(RowView qv, RowVie
     const KeyChunks<float, D> src{seg_rows(kv, sp.seg, B, Hkv, 1), kv.s_token, sp.t_begin, sp.t_end};
     SplitWr<D> wr;
     wr.init(wave, lane, (unsigned)kv.s_token);
-    auto issue = [&](int c) {
+    auto issue = [&](int c, char* slot) {
         const char* rws;
         int valid;
         src(c, &rws, &valid);
-        wr.issue(sh.raw, rws, valid);
+        wr.issue(slot, rws, valid);
     };
-    issue(0);
+    issue(0, sh.raw);
     {
         constexpr int kPerRow = kThreads / kRpg;
         const int r = threadIdx.x / kPerRow, sub = threadIdx.x % kPerRow;
@@ -624,11 +646,13 @@ __global__ __launch_bounds__(kThreads, 2) void snap_pass2_f32(RowView qv, RowVie
             swin[r] = row % W;
         }
     }
+    const char* qseg = seg_rows(qv, sp.seg, B, Hkv, rows / W);
+    const int qr = sp.rg * kRpg + wave * 32 + (lane & 31);  // this lane's query row
     typename S::Frags qf[1];
-    const float uq = load_q_split<D>(qf[0], seg_rows(qv, sp.seg, B, Hkv, rows / W), qv, rows, W,
-                                     sp.rg * kRpg + wave * 32 + (lane & 31), lane);
-    if (lane < 32) srow[wave * 32 + lane] = uq * sl2;
-    __syncthreads();
+    RowMag mag[1];
+    const float ls[1] = {sl2 * S::load_row(qf[0], mag[0], q_row(qseg, qv, rows, W, qr), qr < rows, lane)};
+    if (lane < 32) srow[wave * 32 + lane] = ls[0];
+    const RowMag gmag = S::group_mag(sh, mag, ls, sl2, wave, lane);  // its barrier: sinit, srow and swin written
     f32x16 c_init, c_scale;  // of this lane's 16 rows
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
@@ -654,24 +678,8 @@ __global__ __launch_bounds__(kThreads, 2) void snap_pass2_f32(RowView qv, RowVie
             if (t < sp.t_end) out[t] = (c.x + c.y) + (c.z + c.w);
         }
     };
-#pragma unroll 1
-    for (int s = 0; s < sp.nch; ++s) {
-        wait_vmcnt<0>();
-        // chunk s landed, every wave is done with the planes of chunk s - 1, and
-        // the scol writes of chunk s - 1 are there to be added
-        lds_barrier();
-        S::convert(sh.raw, sh.hi, sh.lo, sh.unscale, wave, lane);
-        if (s >= 1) reduce(s - 1);
-        lds_barrier();  // planes written, raw slot read, sums of chunk s - 1 read
-        if (s + 1 < sp.nch) issue(s + 1);
-        f32x16 acc[1][2];
-        S::template mma<false, 1>(acc, sh.hi, sh.lo, qf, lane);
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-            const float u = sh.unscale[32 * kb + (lane & 31)];  // this lane's key
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[0][kb][i] = fmaf(acc[0][kb][i], u * c_scale[i], c_init[i]);
-        }
+    // sums of exp2(x - lse2) over this wave's rows, per key of chunk s
+    auto add = [&](f32x16 (&acc)[1][2], int s) {
         if (sp.t_begin + (s + 1) * kKeys > min(P_rows, sp.t_end)) {  // past the range end or inside the window
             // key t is visible to window query i (position P_rows + i) iff t - P_rows <= i
 #pragma unroll
@@ -699,6 +707,45 @@ __global__ __launch_bounds__(kThreads, 2) void snap_pass2_f32(RowView qv, RowVie
         }
         interleave_trans<32>();
         scol[s & 1][lane][wave] = lane < 32 ? v[0] : v[1];
+    };
+    int s = 0;
+#pragma unroll 1
+    for (; s < sp.nch; ++s) {
+        if (s > 0) {
+            wait_vmcnt<0>();
+            // chunk s landed, every wave is done with the planes of chunk s - 1, and
+            // the scol writes of chunk s - 1 are there to be added
+            lds_barrier();
+        }
+        S::convert(sh, gmag, wave, lane);
+        if (s >= 1) reduce(s - 1);
+        lds_barrier();  // planes written, raw slot read, sums of chunk s - 1 read
+        if (s + 1 < sp.nch) issue(s + 1, sh.raw);
+        f32x16 acc[1][2];
+        S::template mma<false, 1>(acc, sh, qf, lane);
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+            const float u = sh.unscale[32 * kb + (lane & 31)];  // this lane's key
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[0][kb][i] = fmaf(acc[0][kb][i], u * c_scale[i], c_init[i]);
+        }
+        add(acc, s);
+        if (S::check(s, sp.nch) && S::wide(sh)) break;
+    }
+    if (s < sp.nch) {  // some row was too wide: the sums since the last check are written again, by the same lanes
+        const int s0 = s / S::kCheck * S::kCheck;
+        typename S::FragsF32 qw[1];
+        S::load_row_f32(qw[0], q_row(qseg, qv, rows, W, qr), qr < rows, lane);
+        S::rest_f32(sh, s0, sp.nch, issue, [&](int c, const char* slot) {
+            if (c > s0) reduce(c - 1);
+            f32x16 acc[1][2];
+            S::template mma_f32<false, 1>(acc, slot, qw, lane);
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[0][kb][i] = fmaf(acc[0][kb][i], sl2, c_init[i]);
+            add(acc, c);
+        });
     }
     __syncthreads();
     reduce(sp.nch - 1);

@@ -290,11 +290,11 @@ def test_h2o_score_logit_spikes_match_oracle(K, wl):
     check_scores(f64(score), ref, wl.name)
 
 
-def _f32_logit_bound(q, k, Hkv, scale, lo_terms=3):
+def _f32_logit_bound(q, k, Hkv, scale, lo_terms=8):
     """Largest error of a float32 logit taken as float16 pairs, and twice that
     for a probability (its logit and its row's log-sum-exp): per product the
-    roundings of the two splits and the term left out (2^-24 each), and the
-    sums' 24 roundings per 128 elements, against sum |q| |k|."""
+    roundings of the two splits (2^-23 each) and the term left out (2^-22), and
+    the sums' 24 roundings per 128 elements, against sum |q| |k|."""
     G = q.shape[2] // Hkv
     mass = np.matmul(np.abs(f64(q)), np.abs(np.repeat(f64(k), G, axis=2)).swapaxes(-1, -2)).max()
     return 2 * (lo_terms + 24) * 2.0 ** -24 * scale * mass
@@ -330,6 +330,115 @@ def test_h2o_f32_split_matches_float64(K, N, Hq, Hkv, d, kind):
     assert np.all(np.isfinite(got))
     err = np.abs(got - ref)
     assert np.all(err <= tol * np.abs(ref) + 1e-30), float((err / (np.abs(ref) + 1e-30)).max())
+
+
+def _f32_score_bound(x, q, k, G, keep, d):
+    """Bound of a float32 score's error from its logits' errors, per key: p times
+    the errors of the logit and of its row's log-sum-exp (the error's mean under
+    p), summed over the rows.  A logit is off by D + 8 roundings against its sum
+    |q| |k| (float32 products and sums; fewer for float16 pairs, whose operands
+    and left-out term are 8) and by 2^-22 log2 units where pairs hold small
+    elements to an absolute error.  x, keep: the logits [Hkv, rows, N] in
+    float64 and the causal mask; q [Hkv, rows, d], k [Hkv, N, d]."""
+    x = np.where(keep, x, -np.inf)
+    p = np.exp(x - x.max(-1, keepdims=True))
+    p /= p.sum(-1, keepdims=True)
+    mass = np.matmul(np.abs(q), np.abs(k).swapaxes(-1, -2)) * d ** -0.5
+    e = (d + 8) * 2.0 ** -24 * mass + 2.0 ** -22 * math.log(2.0)
+    e = np.where(keep, e, 0.0)
+    # 3e-6: the exponentials, the sums of probabilities and the statistics' rounding
+    return (p * (e + (p * e).sum(-1, keepdims=True))).sum(1) + 3e-6 * p.sum(1)
+
+
+def _wide_rows(q, k, p, kind, g):
+    """One channel of the keys 2^p times the others (kind "zero": the queries 0
+    there; "inverse": 2^-p), or the queries' channel large and the keys' small
+    ("query"), or in a few of the keys only ("rare")."""
+    c = int(torch.randint(0, k.shape[-1], (1,), generator=g))
+    s = 2.0 ** p
+    if kind == "query":
+        q[..., c] *= s
+        k[..., c] /= s
+    elif kind == "rare":
+        k[..., 3::97, c] *= s
+        q[..., c] /= s
+    else:
+        k[..., c] *= s
+        q[..., c] = 0.0 if kind == "zero" else q[..., c] / s
+    return q, k
+
+
+WIDE = [(6, "zero"), (10, "inverse"), (13, "zero"), (16, "inverse"), (20, "query"), (24, "zero"), (24, "rare"),
+        (30, "rare"), (38, "zero"), (60, "inverse"), (100, "query")]
+
+
+@pytest.mark.parametrize("N,Hq,Hkv,d", [(1, 1, 1, 64), (65, 3, 1, 64), (300, 2, 1, 128), (530, 6, 2, 128)])
+@pytest.mark.parametrize("p,kind", WIDE)
+def test_h2o_f32_rows_of_wide_range(K, N, Hq, Hkv, d, p, kind):
+    """Float32 rows whose elements span more than a float16 pair holds: the
+    scores stay as close to their 64-bit values as float32 products are."""
+    note(f"h2o f32 wide N={N} Hq={Hq} Hkv={Hkv} d={d} 2^{p} {kind}")
+    g = torch.Generator().manual_seed(N + d + p)
+    q, k = _wide_rows(torch.randn((1, 1, Hq, N, d), generator=g), torch.randn((1, 1, Hkv, N, d), generator=g), p, kind,
+                      g)
+    score = K.h2o_score(q.cuda(), k.cuda())
+    torch.cuda.synchronize()
+    G = Hq // Hkv
+    ref = O.h2o_score(f64(q), f64(k), Hkv)
+    qs, ks = f64(q)[0, 0].reshape(Hkv, G * N, d), f64(k)[0, 0]
+    keep = np.tile(np.tril(np.ones((N, N), dtype=bool)), (G, 1))[None]
+    tol = _f32_score_bound(np.matmul(qs, ks.swapaxes(-1, -2)) * d ** -0.5, qs, ks, G, keep, d)
+    err = np.abs(f64(score) - ref)[0, 0]
+    assert np.all(err <= tol + 1e-30), float((err / (tol + 1e-30)).max())
+
+
+@pytest.mark.parametrize("N,Hq,Hkv,W,d", [(64, 1, 1, 16, 128), (129, 3, 1, 16, 64), (1000, 8, 1, 32, 64),
+                                          (5003, 4, 1, 8, 128)])
+@pytest.mark.parametrize("p,kind", WIDE)
+def test_snapkv_f32_rows_of_wide_range(K, N, Hq, Hkv, W, d, p, kind):
+    """As for H2O, both passes and pass 2 alone (window statistics supplied)."""
+    note(f"snapkv f32 wide N={N} Hq={Hq} Hkv={Hkv} W={W} d={d} 2^{p} {kind}")
+    g = torch.Generator().manual_seed(N + d + p)
+    q, k = _wide_rows(torch.randn((1, 1, Hq, W, d), generator=g), torch.randn((1, 1, Hkv, N, d), generator=g), p, kind,
+                      g)
+    G = Hq // Hkv
+    ref = O.snapkv_score(f64(q), f64(k), Hkv, 1)
+    qs, ks = f64(q)[0, 0].reshape(Hkv, G * W, d), f64(k)[0, 0]
+    keep = np.tile(np.arange(N) <= np.arange(N - W, N)[:, None], (G, 1))[None]
+    x = np.matmul(qs, ks.swapaxes(-1, -2)) * d ** -0.5
+    tol = _f32_score_bound(x, qs, ks, G, keep, d)
+    xm = np.where(keep, x, -np.inf)
+    top = xm.max(-1, keepdims=True)
+    lse = (np.log(np.exp(xm - top).sum(-1)) + top[..., 0]).reshape(1, 1, Hq, W)
+    lse = torch.from_numpy(lse).float().cuda()
+    for name, score in (("both", run_snapkv(K, q.cuda(), k.cuda(), 1)), ("lse", K.snapkv_score_lse(q.cuda(), k.cuda(), lse, 1))):
+        torch.cuda.synchronize()
+        # a supplied log-sum-exp carries float32's rounding of its own magnitude
+        t = tol + (0.0 if name == "both" else 2.0 ** -24 * float(lse.abs().max()) * ref[0, 0])
+        err = np.abs(f64(score) - ref)[0, 0]
+        assert np.all(err <= t + 1e-30), (name, float((err / (t + 1e-30)).max()))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("N", [65, 700])
+def test_f32_infinities_of_opposite_sign_give_nan(K, N, d):
+    """A key with +inf and -inf elements beside queries of one sign: its logits
+    are NaN in float32, and so is its score, in both scorers; the keys before it
+    keep theirs in a call without it."""
+    note(f"f32 opposite infinities N={N} d={d}")
+    g = torch.Generator().manual_seed(N + d)
+    q, k = torch.randn((1, 1, 2, N, d), generator=g), torch.randn((1, 1, 1, N, d), generator=g)
+    q[..., 3:5] = q[..., 3:5].abs() + 0.1
+    t = N - 20  # a window position: the pool's maximum leaves NaN out
+    k[..., t, 3], k[..., t, 4] = math.inf, -math.inf
+    for name, W, score in (("h2o", N, K.h2o_score(q.cuda(), k.cuda())),
+                           ("snapkv", 32, run_snapkv(K, q[:, :, :, -32:].contiguous().cuda(), k.cuda(), 1))):
+        torch.cuda.synchronize()
+        assert math.isnan(float(score[0, 0, 0, t])), name
+    # rows before t alone: the score of the last of them is its own row's
+    short = K.h2o_score(q[:, :, :, :t].contiguous().cuda(), k[:, :, :, :t].contiguous().cuda())
+    torch.cuda.synchronize()
+    check_scores(f64(short), O.h2o_score(f64(q[:, :, :, :t]), f64(k[:, :, :, :t]), 1), "rows before the infinities")
 
 
 def _token_major(x, pad):
