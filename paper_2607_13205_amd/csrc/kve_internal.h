@@ -5,6 +5,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "kve_decode_plan.h"
 #include "kve_snap_plan.h"
 
 namespace kve {
@@ -26,50 +27,6 @@ inline size_t h2o_colsum_offset(int L, int B, int Hq, int N) {
 
 inline size_t h2o_workspace(int L, int B, int Hq, int N) {
     return h2o_colsum_offset(L, B, Hq, N) * sizeof(float) + align_up((size_t)L * B * Hq * N * sizeof(float));
-}
-
-// ---------------------------------------------------------------------------
-// Decode over a compacted cache: the k_cap rows of a segment are cut into
-// splits of whole kDecodeQuantum-row quanta, one workgroup each (about
-// kDecodeTargetGroups workgroups in all); each writes per head the partial
-// output o[d] and its (reference, denominator) pair, merged by a last step.
-// One workgroup per compute unit: more splits only add starts and partials to
-// merge (bf16, d = 128: 128 segments of 1639 rows take 21 us at 256 workgroups
-// and 24 at 1024, 8 of 32768 25.8 and 27.9, 2 of 20000 14.0 and 16.9; float32,
-// 32 of 5000 30.8 and 37.4; 256 of 6000 134 and 136).  The workspace is sized
-// for kDecodeSizeGroups, as it always was.
-// ---------------------------------------------------------------------------
-constexpr int kDecodeQuantum = 128;
-constexpr int kDecodeTargetGroups = 256;
-constexpr int kDecodeSizeGroups = 1024;
-constexpr int kDecodeMaxGroup = 8;  // query heads per KV head
-
-struct DecodePlan {
-    int segs, G, nsplit, split_keys;
-    size_t off_o, off_ml, total;
-};
-
-inline DecodePlan decode_plan(int L, int B, int Hq, int Hkv, int k_cap, int d) {
-    DecodePlan p{};
-    p.segs = L * B * Hkv;
-    p.G = Hq / Hkv;
-    const long long quanta = (k_cap + kDecodeQuantum - 1) / kDecodeQuantum;
-    // quanta per split and splits for a number of workgroups
-    auto splits = [&](int groups, long long& per) {
-        long long ns = (groups + p.segs - 1) / p.segs;
-        if (ns > quanta) ns = quanta;
-        if (ns < 1) ns = 1;
-        per = (quanta + ns - 1) / ns;
-        return (quanta + per - 1) / per;
-    };
-    long long per;
-    const size_t parts = (size_t)p.segs * splits(kDecodeSizeGroups, per) * p.G;
-    p.nsplit = (int)splits(kDecodeTargetGroups, per);
-    p.split_keys = (int)(per * kDecodeQuantum);
-    p.off_o = 0;
-    p.off_ml = align_up(parts * d * sizeof(float));
-    p.total = p.off_ml + align_up(parts * 2 * sizeof(float));
-    return p;
 }
 
 // ---------------------------------------------------------------------------

@@ -262,6 +262,50 @@ def test_snapkv_rejects_more_window_rows_than_supported_before_any_launch(kve):
     assert st == kve.binding.KVE_ERR_WORKSPACE
 
 
+DECODE_PLAN_PROGRAM = """
+#include <cstdio>
+#include <cstdlib>
+#include "kve_decode_plan.h"
+int main(int argc, char** argv) {
+    for (int i = 1; i + 1 < argc; i += 2) {
+        const kve::DecodePlan p = kve::decode_plan(1, atoi(argv[i]), 4, 1, atoi(argv[i + 1]), 128);
+        printf("%d %d %zu\\n", p.nsplit, p.split_keys / kve::kDecodeQuantum, p.off_ml);
+    }
+}
+"""
+
+
+def test_decode_splits_fill_the_compute_units(tmp_path):
+    """Splits cover the cache and fit the workspace; unless they are already as
+    short as three workgroups per compute unit make them, none is longer than 16
+    quanta (the counts of a batch differ) and the rounds of one workgroup per
+    unit are at least 0.85 full."""
+    import os
+    import shutil
+    import subprocess
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("no g++")
+    src = tmp_path / "plan.cpp"
+    src.write_text(DECODE_PLAN_PROGRAM)
+    csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2607_13205_amd", "csrc")
+    exe = str(tmp_path / "plan")
+    subprocess.run([cxx, "-std=c++17", "-I", csrc, str(src), "-o", exe], check=True)
+    cases = [(s, k) for s in (1, 2, 7, 8, 31, 32, 64, 100, 128, 136, 160, 200, 248, 255, 256, 257, 264, 288, 320, 384,
+                              448, 504, 512, 513, 640, 800, 1016, 1023, 1024, 1025, 5000)
+             for k in (1, 127, 128, 129, 1639, 2048, 2049, 6000, 20000, 32768, 200001)]
+    out = subprocess.run([exe] + [str(x) for c in cases for x in c], check=True, capture_output=True, text=True).stdout
+    for (segs, k_cap), line in zip(cases, out.split("\n")):
+        ns, per, room = (int(x) for x in line.split())
+        quanta = -(-k_cap // 128)
+        assert ns * per >= quanta > (ns - 1) * per, (segs, k_cap, line)
+        assert segs * ns * 4 * 128 * 4 <= room, (segs, k_cap, line)
+        rounds = -(-segs * ns // 256)
+        even = rounds == 1 or segs * ns >= 0.85 * 256 * rounds
+        least_of_three = -(-quanta // min(quanta, -(-768 // segs)))  # quanta per split at three workgroups per unit
+        assert (per <= 16 and even) or per <= least_of_three, (segs, k_cap, line)
+
+
 @pytest.mark.parametrize("L,B,Hq,Hkv,N,W,d", [(1, 1, 2, 1, 512, 16, 64), (1, 1, 32, 8, 8192, 32, 128),
                                               (8, 2, 32, 8, 20011, 32, 128), (1, 1, 32, 8, 131072, 64, 128),
                                               (32, 4, 32, 8, 32768, 32, 128), (2, 3, 12, 3, 5003, 50, 64)])

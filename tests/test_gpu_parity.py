@@ -1216,6 +1216,27 @@ def test_decode_merge_of_many_splits(K, Hq, Hkv, k_cap, d, dt):
     check_decode(out.cpu().numpy(), ref, ref_abs, xmax, f"decode merge {k_cap}")
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,k_cap,d,dt", [
+    (17, 8, 8, 1639, 64, "bf16"),   # 136 segments: splits of three quanta, rounds of workgroups nearly full
+    (33, 8, 8, 700, 128, "f32"),    # 264: two splits of three quanta
+    (65, 4, 4, 2100, 64, "bf16"),   # 260: no split above 16 quanta
+    (200, 4, 4, 900, 64, "f32")])   # 800: two splits each
+def test_decode_many_segments_of_unequal_counts(K, B, Hq, Hkv, k_cap, d, dt):
+    """Batches whose counts differ several times over, at segment counts around
+    and above the number of compute units."""
+    note(f"decode unequal {B} {Hkv} {k_cap} {d} {dt}")
+    tdt = torch.bfloat16 if dt == "bf16" else torch.float32
+    g = torch.Generator().manual_seed(k_cap + B)
+    q = (2.0 * torch.randn((1, B, Hq, d), generator=g)).to(tdt)
+    kc, vc = (torch.randn((1, B, Hkv, k_cap, d), generator=g).to(tdt) for _ in range(2))
+    n = np.array([(k_cap, k_cap // 10, 1, k_cap // 3)[b % 4] for b in range(B)], dtype=np.int32)
+    count = np.broadcast_to(n[None, :, None], (1, B, Hkv)).copy()
+    out = K.decode_attention(q.cuda(), kc.cuda(), vc.cuda(), torch.from_numpy(count).cuda())
+    torch.cuda.synchronize()
+    ref, ref_abs, xmax = _decode_ref(f64(q), f64(kc), f64(vc), count)
+    check_decode(out.cpu().numpy(), ref, ref_abs, xmax, f"decode unequal {B}x{Hkv} {k_cap}")
+
+
 def test_decode_explicit_scale_and_repeat(K):
     L, B, Hq, Hkv, k_cap, d = 1, 2, 8, 2, 400, 128
     g = torch.Generator(device="cpu")
