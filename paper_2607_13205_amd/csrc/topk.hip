@@ -40,6 +40,7 @@
 
 #include "kve_device.h"
 #include "kve_internal.h"
+#include "kve_topk_plan.h"
 
 namespace kve {
 namespace {
@@ -53,9 +54,6 @@ constexpr int kLowBits = 32 - kDigitBits;  // key bits below the top digit
 constexpr uint32_t kLowMask = (1u << kLowBits) - 1u;
 constexpr int kSpan = 16;                  // consecutive positions per lane and step
 constexpr int kWaveStep = kWave * kSpan;   // positions per wave step
-// longest segment topk_regs holds: 16 keys per thread of 1024 (at 32 the keys
-// spill; 1024 segments of 16384 keys take 62 us either way)
-constexpr int kRegsMax = 16384;
 constexpr int kBatch = 8;                  // staged entries per lane loaded before use
 constexpr uint32_t kNoKey = 0xffffffffu;   // above every key (+inf maps to 0xff800000)
 constexpr uint32_t kKept = 0xffffffffu;    // tag of a staged position that is surely kept
@@ -179,6 +177,7 @@ __device__ __forceinline__ void load_span_any(const float* sc, const int8_t* ro,
 template <int SPAN, typename F>
 __device__ __forceinline__ void count_runs(uint32_t* hist, F&& bin_of) {
     constexpr int G = SPAN < 8 ? SPAN : 8;
+    static_assert(SPAN % G == 0, "whole groups");
     uint32_t cur = kNoKey, cnt = 0u;
 #pragma unroll
     for (int g = 0; g < SPAN; g += G) {
@@ -493,7 +492,8 @@ __global__ __launch_bounds__(NT) void topk_kernel(const float* __restrict__ scor
 //                every workgroup) stages the slice's kept and undecided keys in
 //                order; one workgroup per segment finds the other digits over
 //                the staged keys and writes the output.  8 x 100003: 175 -> 40
-//                us, 8 x 131072: 90 -> 44 us, 64 x 40001: 86 -> 35 us.
+//                us, 8 x 131072: 90 -> 44 us, 64 x 40001: 86 -> 35 us (four
+//                buckets).
 // ---------------------------------------------------------------------------
 
 // exclusive prefix sum of one value per thread over a workgroup of NW waves;
@@ -613,14 +613,11 @@ __global__ __launch_bounds__(NT) void topk_regs(const float* __restrict__ score,
 constexpr int kSplitThreads = 1024;
 constexpr int kSplitSpan = 16;
 constexpr int kSplitStep = kSplitThreads * kSplitSpan;
-constexpr int kMaxSlices = 64;
-// segments up to which a split pays: 64 x 65536 keys take 51 us split and 60
-// whole, 64 x 131072 91 and 94; 256 x 65536 127 and 73 (the slices' workgroups
-// of 16 waves, one per CU, then queue for the chip)
-constexpr size_t kSplitSegs = 64;
-constexpr int kHold = 32;  // staged keys per lane of topk_finish held in registers
+// staged keys per lane of topk_finish held in registers; with one bucket 32 of
+// them spill (69 registers; 64 x 40001 keys 35.7 us, 31.5 with 16)
+template <int R>
+constexpr int kHoldOf = R == 1 ? 16 : 32;
 constexpr int kSliceWords = 4 + 3 * kRoleHistMaxR;  // lowest bin, bins' end, staged keys, -, buckets of the segment
-constexpr int kSliceMinPad = 128;
 static_assert(2 * kSliceMinPad >= 16 + 4 * kSliceWords + 32, "a record fits the slice's spare bytes");
 
 // first position of slice s of S (a multiple of 16; N for s = S); N < 2^22 + 2^16, S <= kMaxSlices
@@ -819,7 +816,7 @@ template <int R>
 __global__ __launch_bounds__(kSplitThreads) void topk_finish(int N, int S, int k_cap, const char* __restrict__ ws,
                                                              int32_t* __restrict__ idx_out,
                                                              int32_t* __restrict__ count_out) {
-    constexpr int NW = kSplitThreads / kWave;
+    constexpr int NW = kSplitThreads / kWave, kHold = kHoldOf<R>;
     __shared__ __align__(16) uint32_t hist[R * kDigits];
     __shared__ Bucket bk[R + 1];
     __shared__ uint32_t top[R];          // first digit of the undecided keys
@@ -1114,7 +1111,7 @@ hipError_t launch_topk(const float* score, const int8_t* roles, const int32_t* q
                        int L, int B, int Hkv, int N, int W, int R, int k_cap, int32_t* idx_out, int32_t* count_out,
                        void* ws, hipStream_t st) {
     const size_t segs = (size_t)L * B * Hkv;
-    if (hist == nullptr && N <= kRegsMax) {
+    if (hist == nullptr && topk_in_regs(N)) {
         switch (R) {
 #define KVE_TOPK_CASE(RR) \
     case RR:              \
@@ -1125,8 +1122,8 @@ hipError_t launch_topk(const float* score, const int8_t* roles, const int32_t* q
                 return hipErrorInvalidValue;
         }
     }
-    const int slices = std::min(N / (kDigits * R + kSliceMinPad), kMaxSlices);
-    if (hist == nullptr && segs <= kSplitSegs && slices > 1 && N <= kMaxSlices * 65504) {
+    const int slices = hist == nullptr ? topk_slices(segs, N, R) : 0;
+    if (slices > 1) {
         switch (R) {
 #define KVE_TOPK_CASE(RR)                                                                                       \
     case RR:                                                                                                    \

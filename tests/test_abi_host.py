@@ -262,6 +262,54 @@ def test_snapkv_rejects_more_window_rows_than_supported_before_any_launch(kve):
     assert st == kve.binding.KVE_ERR_WORKSPACE
 
 
+def _run_plan(tmp_path, program, args):
+    """Lines that a program over one of the plain C++ plan headers prints."""
+    import os
+    import shutil
+    import subprocess
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("no g++")
+    src, exe = tmp_path / "plan.cpp", str(tmp_path / "plan")
+    src.write_text(program)
+    csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2607_13205_amd", "csrc")
+    subprocess.run([cxx, "-std=c++17", "-I", csrc, str(src), "-o", exe], check=True)
+    out = subprocess.run([exe] + [str(x) for a in args for x in a], check=True, capture_output=True, text=True).stdout
+    return out.strip().split("\n")
+
+
+TOPK_PLAN_PROGRAM = """
+#include <cstdio>
+#include <cstdlib>
+#include "kve_topk_plan.h"
+int main(int argc, char** argv) {
+    for (int i = 1; i + 2 < argc; i += 3) {
+        const int segs = atoi(argv[i]), N = atoi(argv[i + 1]), R = atoi(argv[i + 2]);
+        printf("%d %d\\n", (int)kve::topk_in_regs(N), kve::topk_slices(segs, N, R));
+    }
+}
+"""
+
+
+def test_topk_slices_fit_the_chip_and_their_records(tmp_path):
+    """Slices of split segments: one workgroup per compute unit for all of them
+    (two per segment at least) unless 16-bit offsets need more, each with room
+    for its counts (8 bytes per position: tags, offsets and 16-bit counts)."""
+    cases = [(s, n, r) for s in (1, 2, 7, 8, 16, 33, 64, 65, 256) for r in (1, 2, 4, 8)
+             for n in (4096, 16384, 16385, 24000, 40001, 65536, 131071, 262144, 270001, 1000000, 4192256, 4192257)]
+    for (segs, n, r), line in zip(cases, _run_plan(tmp_path, TOPK_PLAN_PROGRAM, cases)):
+        regs, s = (int(x) for x in line.split())
+        assert regs == (n <= 16384), (segs, n, r)
+        if s == 0:
+            assert segs > 64 or n > 64 * 65504 or n < 2 * max(4096, 2048 * r + 128), (segs, n, r)
+            continue
+        assert 2 <= s <= 64 and segs <= 64
+        shortest, longest = n // 16 // s * 16, n // 16 // s * 16 + 32
+        assert longest <= 65536, (segs, n, r, s)
+        assert 2 * shortest >= 2 * 2048 * r + 16 + 112, (segs, n, r, s)
+        assert s * segs <= max(256, 2 * segs) or s == -(-n // 65504), (segs, n, r, s)
+
+
 DECODE_PLAN_PROGRAM = """
 #include <cstdio>
 #include <cstdlib>
@@ -280,22 +328,10 @@ def test_decode_splits_fill_the_compute_units(tmp_path):
     short as three workgroups per compute unit make them, none is longer than 16
     quanta (the counts of a batch differ) and the rounds of one workgroup per
     unit are at least 0.85 full."""
-    import os
-    import shutil
-    import subprocess
-    cxx = shutil.which("g++")
-    if cxx is None:
-        pytest.skip("no g++")
-    src = tmp_path / "plan.cpp"
-    src.write_text(DECODE_PLAN_PROGRAM)
-    csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2607_13205_amd", "csrc")
-    exe = str(tmp_path / "plan")
-    subprocess.run([cxx, "-std=c++17", "-I", csrc, str(src), "-o", exe], check=True)
     cases = [(s, k) for s in (1, 2, 7, 8, 31, 32, 64, 100, 128, 136, 160, 200, 248, 255, 256, 257, 264, 288, 320, 384,
                               448, 504, 512, 513, 640, 800, 1016, 1023, 1024, 1025, 5000)
              for k in (1, 127, 128, 129, 1639, 2048, 2049, 6000, 20000, 32768, 200001)]
-    out = subprocess.run([exe] + [str(x) for c in cases for x in c], check=True, capture_output=True, text=True).stdout
-    for (segs, k_cap), line in zip(cases, out.split("\n")):
+    for (segs, k_cap), line in zip(cases, _run_plan(tmp_path, DECODE_PLAN_PROGRAM, cases)):
         ns, per, room = (int(x) for x in line.split())
         quanta = -(-k_cap // 128)
         assert ns * per >= quanta > (ns - 1) * per, (segs, k_cap, line)

@@ -553,12 +553,14 @@ def test_topk_many_segments_take_the_four_wave_workgroups(K, R, N):
 
 
 # (segments as L, B, Hkv), N, R: the whole-segment kernel at the edges of its
-# forms (4, 8 and 16 keys per thread), the split kernels (two slices up to 15,
-# ragged last ones, eight buckets), the general kernel where a segment is too
+# forms (4, 8 and 16 keys per thread), the split kernels (two slices up to 64,
+# ragged last ones, eight buckets, few slices of many segments, slices as long as
+# 16-bit offsets allow), the general kernel where a segment is too
 # short to split, where segments are many (16-wave and 4-wave workgroups)
 TOPK_ROUTES = [((1, 1, 2), 1025, 4), ((1, 1, 2), 4096, 2), ((1, 1, 2), 4097, 8), ((1, 2, 1), 8193, 4),
                ((1, 1, 2), 16384, 4), ((1, 1, 2), 16385, 4), ((1, 1, 1), 16385, 8), ((1, 2, 1), 33025, 8),
-               ((1, 1, 2), 70001, 4), ((1, 1, 1), 131071, 1), ((1, 1, 65), 16385, 4), ((4, 2, 64), 16387, 4)]
+               ((1, 1, 2), 70001, 4), ((1, 1, 1), 131071, 1), ((1, 1, 65), 16385, 4), ((4, 2, 64), 16387, 4),
+               ((1, 1, 1), 262147, 1), ((1, 1, 64), 17000, 1), ((1, 1, 64), 270001, 2)]
 
 
 @pytest.mark.parametrize("segs,N,R", TOPK_ROUTES)
