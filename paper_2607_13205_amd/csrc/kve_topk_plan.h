@@ -12,8 +12,19 @@ namespace kve {
 // topk_regs: whole segments in registers, 16 keys per thread of 1024 at most (at
 // 32 the keys spill; 1024 segments of 16384 keys take 62 us either way).
 constexpr int kRegsMax = 16384;
+// Many segments of more than kRegsShort keys and few buckets: topk_kernel's
+// workgroups of four waves use the chip better than topk_regs' of sixteen, of
+// which two share a compute unit and end together (2048 segments of 12000 keys,
+// four buckets: 84 us and 112, 16384 keys 103 and 120; with eight buckets, whose
+// histograms leave two workgroups per unit either way, 140 and 126; 768 segments
+// of 12000, where topk_kernel does not fill the chip, 51 and 46).
+constexpr int kRegsShort = 8192;
+constexpr size_t kRegsSegs = 1024;
+constexpr int kRegsFewBuckets = 4;
 
-inline bool topk_in_regs(int N) { return N <= kRegsMax; }
+inline bool topk_in_regs(size_t segs, int N, int R) {
+    return N <= kRegsShort || (N <= kRegsMax && !(segs >= kRegsSegs && R <= kRegsFewBuckets));
+}
 
 // Segments split into slices, one workgroup each (topk_count, topk_stage), up to
 // kSplitSegs segments: 64 x 65536 keys take 48 us split and 60 whole, 64 x

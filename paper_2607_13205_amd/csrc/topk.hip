@@ -5,11 +5,12 @@
 // Scores are mapped to order-preserving 32-bit keys (-0 -> +0, NaN lowest), and
 // each bucket's quota-th largest key is found digit by digit (11, 11 and 10
 // bits) from LDS histograms.  Three forms, by size (launch_topk):
-//   topk_regs    a segment (layer, sample, KV head) of up to 16384 keys: one
+//   topk_regs    a segment (layer, sample, KV head) of up to 16384 keys (8192
+//                when there are many segments and few buckets): one
 //                workgroup with the whole segment in registers.
 //   topk_count, topk_stage, topk_finish
 //                up to 64 longer segments, each split over several workgroups.
-//   topk_kernel  many longer segments, or scores with fused histograms: one
+//   topk_kernel  many longer ones, or scores with fused histograms: one
 //                workgroup per segment, of 4 waves, or of 16 when there are too
 //                few segments to fill the chip with 4-wave ones; two sweeps over
 //                the segment's scores and labels:
@@ -1111,7 +1112,7 @@ hipError_t launch_topk(const float* score, const int8_t* roles, const int32_t* q
                        int L, int B, int Hkv, int N, int W, int R, int k_cap, int32_t* idx_out, int32_t* count_out,
                        void* ws, hipStream_t st) {
     const size_t segs = (size_t)L * B * Hkv;
-    if (hist == nullptr && topk_in_regs(N)) {
+    if (hist == nullptr && topk_in_regs(segs, N, R)) {
         switch (R) {
 #define KVE_TOPK_CASE(RR) \
     case RR:              \

@@ -285,7 +285,7 @@ TOPK_PLAN_PROGRAM = """
 int main(int argc, char** argv) {
     for (int i = 1; i + 2 < argc; i += 3) {
         const int segs = atoi(argv[i]), N = atoi(argv[i + 1]), R = atoi(argv[i + 2]);
-        printf("%d %d\\n", (int)kve::topk_in_regs(N), kve::topk_slices(segs, N, R));
+        printf("%d %d\\n", (int)kve::topk_in_regs(segs, N, R), kve::topk_slices(segs, N, R));
     }
 }
 """
@@ -295,11 +295,11 @@ def test_topk_slices_fit_the_chip_and_their_records(tmp_path):
     """Slices of split segments: one workgroup per compute unit for all of them
     (two per segment at least) unless 16-bit offsets need more, each with room
     for its counts (8 bytes per position: tags, offsets and 16-bit counts)."""
-    cases = [(s, n, r) for s in (1, 2, 7, 8, 16, 33, 64, 65, 256) for r in (1, 2, 4, 8)
-             for n in (4096, 16384, 16385, 24000, 40001, 65536, 131071, 262144, 270001, 1000000, 4192256, 4192257)]
+    cases = [(s, n, r) for s in (1, 2, 7, 8, 16, 33, 64, 65, 256, 1023, 1024) for r in (1, 2, 4, 5, 8)
+             for n in (4096, 8192, 8193, 16384, 16385, 24000, 40001, 65536, 131071, 262144, 270001, 1000000, 4192256, 4192257)]
     for (segs, n, r), line in zip(cases, _run_plan(tmp_path, TOPK_PLAN_PROGRAM, cases)):
         regs, s = (int(x) for x in line.split())
-        assert regs == (n <= 16384), (segs, n, r)
+        assert regs == (n <= (8192 if segs >= 1024 and r <= 4 else 16384)), (segs, n, r)
         if s == 0:
             assert segs > 64 or n > 64 * 65504 or n < 2 * max(4096, 2048 * r + 128), (segs, n, r)
             continue

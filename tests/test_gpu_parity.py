@@ -556,11 +556,13 @@ def test_topk_many_segments_take_the_four_wave_workgroups(K, R, N):
 # forms (4, 8 and 16 keys per thread), the split kernels (two slices up to 64,
 # ragged last ones, eight buckets, few slices of many segments, slices as long as
 # 16-bit offsets allow), the general kernel where a segment is too
-# short to split, where segments are many (16-wave and 4-wave workgroups)
+# short to split, where segments are many (16-wave and 4-wave workgroups, the
+# latter from 8193 keys on at 1024 segments of up to four buckets)
 TOPK_ROUTES = [((1, 1, 2), 1025, 4), ((1, 1, 2), 4096, 2), ((1, 1, 2), 4097, 8), ((1, 2, 1), 8193, 4),
                ((1, 1, 2), 16384, 4), ((1, 1, 2), 16385, 4), ((1, 1, 1), 16385, 8), ((1, 2, 1), 33025, 8),
                ((1, 1, 2), 70001, 4), ((1, 1, 1), 131071, 1), ((1, 1, 65), 16385, 4), ((4, 2, 64), 16387, 4),
-               ((1, 1, 1), 262147, 1), ((1, 1, 64), 17000, 1), ((1, 1, 64), 270001, 2)]
+               ((1, 1, 1), 262147, 1), ((1, 1, 64), 17000, 1), ((1, 1, 64), 270001, 2), ((4, 4, 64), 8193, 4),
+               ((4, 4, 64), 8195, 5)]
 
 
 @pytest.mark.parametrize("segs,N,R", TOPK_ROUTES)
