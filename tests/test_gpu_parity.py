@@ -490,8 +490,9 @@ def _random_selection_case(rng, N, R_labels, R):
     return s, roles
 
 
-def _topk_check(K, score, roles, quota, W, R, roles_dev=None, score_dev=None):
-    """Run the GPU top-k on host arrays and compare every segment with the oracle."""
+def _topk_check(K, score, roles, quota, W, R, roles_dev=None, score_dev=None, distinct=None):
+    """Run the GPU top-k on host arrays and compare every segment with the oracle
+    (distinct: KV heads repeat after that many, and layers are alike)."""
     L, B, Hkv, N = score.shape
     kept = [W + sum(min(max(int(quota[b, r]), 0), int(np.sum(roles[b, :N - W] == r)))
                     for r in range(R)) for b in range(B)]
@@ -501,10 +502,14 @@ def _topk_check(K, score, roles, quota, W, R, roles_dev=None, score_dev=None):
     idx, cnt = K.topk_select(sd, rd, torch.from_numpy(quota).cuda(), W, R, k_cap)
     torch.cuda.synchronize()
     idx, cnt = idx.cpu().numpy(), cnt.cpu().numpy()
+    seen = {}
     for l in range(L):
         for b in range(B):
             for j in range(Hkv):
-                ref = O.select_keep(score[l, b, j], roles[b], quota[b], W)
+                key = (l, b, j) if distinct is None else (b, j % distinct)
+                if key not in seen:
+                    seen[key] = O.select_keep(score[l, b, j], roles[b], quota[b], W)
+                ref = seen[key]
                 assert cnt[l, b, j] == len(ref) == kept[b], (l, b, j)
                 assert idx[l, b, j, :len(ref)].tolist() == ref.tolist(), (l, b, j)
 
@@ -534,9 +539,10 @@ def test_topk_select_bit_exact_with_oracle(K, R, layout):
     _topk_check(K, score, roles, quota, W, R)
 
 
-@pytest.mark.parametrize("R,N", [(4, 301), (4, 304), (8, 1000), (1, 4096)])
+@pytest.mark.parametrize("R,N", [(4, 301), (4, 304), (8, 1000), (1, 4096), (1, 16400), (3, 16389), (8, 16385)])
 def test_topk_many_segments_take_the_four_wave_workgroups(K, R, N):
-    """512 segments and more use four-wave workgroups (fewer use sixteen waves)."""
+    """512 segments: in registers up to 16384 keys, by the general kernel's
+    four-wave workgroups above (fewer segments use sixteen waves)."""
     rng = np.random.default_rng(60 + R + N)
     L, B, Hkv = 4, 4, 32
     W = 20
@@ -615,10 +621,19 @@ def test_topk_very_short_rows(K, N, W):
         assert idx.shape[-1] == 0 and not cnt.cpu().numpy().any()
 
 
-def test_topk_misaligned_rows_take_the_per_position_loads(K):
+# segments and a length for each form of the selection: in registers, split over
+# workgroups, one workgroup of sixteen waves, one of four, and four-wave
+# workgroups below the registers' limit
+TOPK_FORMS = {"regs": ((1, 2, 2), 2048), "split": ((1, 2, 1), 33040), "wide": ((1, 2, 33), 16400),
+              "narrow": ((4, 2, 64), 16400), "many": ((8, 2, 64), 8208)}
+
+
+@pytest.mark.parametrize("form", TOPK_FORMS)
+def test_topk_misaligned_rows_take_the_per_position_loads(K, form):
     """N a multiple of 16 but the score and label rows not 16-byte aligned."""
     rng = np.random.default_rng(41)
-    L, B, Hkv, N, R, W = 1, 2, 2, 4096, 4, 32
+    (L, B, Hkv), N = TOPK_FORMS[form]
+    R, W = 4, 32
     score = rng.random((L, B, Hkv, N)).astype(np.float32)
     roles = rng.integers(0, R, (B, N)).astype(np.int8)
     quota = rng.integers(0, N // R, (B, R)).astype(np.int32)
@@ -632,15 +647,18 @@ def test_topk_misaligned_rows_take_the_per_position_loads(K):
 
 
 @pytest.mark.parametrize("case", ["all_equal", "all_nan", "two_values", "window_only", "no_window",
-                                  "one_bin", "inf", "nan_below_neginf"])
-def test_topk_degenerate_inputs(K, case):
-    """Every key in the threshold's bin, every key tied, no prefix, no window."""
+                                  "one_bin", "inf", "nan_below_neginf", "half_window"])
+@pytest.mark.parametrize("form", TOPK_FORMS)
+def test_topk_degenerate_inputs(K, form, case):
+    """Every key in the threshold's bin, every key tied, no prefix, no window, a
+    window that holds whole slices, in each form of the selection.  Many segments
+    repeat 16 of them."""
     rng = np.random.default_rng(50)
-    L, B, Hkv, N, R = 1, 2, 2, 2048, 3
-    W = 16
+    (L, B, Hkv), N = TOPK_FORMS[form]
+    R, W, m = 3, 16, N // 2048  # the quotas are those of 2048 keys, m times
     score = rng.random((L, B, Hkv, N)).astype(np.float32)
     roles = rng.integers(0, R, (B, N)).astype(np.int8)
-    quota = np.array([[100, 0, 700], [1, 2000, 5]], dtype=np.int32)
+    quota = np.array([[100 * m, 0, 700 * m], [1, 2000 * m, 5]], dtype=np.int32)
     if case == "all_equal":
         score[:] = 0.25
     elif case == "all_nan":
@@ -663,8 +681,14 @@ def test_topk_degenerate_inputs(K, case):
         u = rng.random(score.shape)
         score[u < 0.45] = -np.inf
         score[u > 0.55] = np.nan
-        quota = np.array([[400, 0, 350], [1, 2000, 380]], dtype=np.int32)
-    _topk_check(K, score, roles, quota, W, R)
+        quota = np.array([[400 * m, 0, 350 * m], [1, 2000 * m, 380 * m]], dtype=np.int32)
+    elif case == "half_window":
+        W = N // 2
+    distinct = 8  # KV heads that differ
+    for j in range(distinct, Hkv):
+        score[:, :, j] = score[:, :, j % distinct]
+    score[1:] = score[0]
+    _topk_check(K, score, roles, quota, W, R, distinct=distinct)
 
 
 def test_topk_reports_truncation(K):
