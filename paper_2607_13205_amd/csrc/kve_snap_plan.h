@@ -52,18 +52,29 @@ constexpr size_t kSnapScratchBytes = (size_t)64 << 20;
 // chunk's latency) costs about four chunks of its time, and a pass ends when
 // the fullest compute unit does: of the range sizes that give at most k
 // workgroups per unit, k = 1 .. 16, the one with the least
-//   ceil(workgroups / units) (chunks per range + 4)
-// is taken, a single workgroup per unit counting its chunks 1.25 times (nothing
-// hides its latencies; float32, whose chunks are split between barriers, 1.4
-// times: N = 32768 takes 98 us at 16 chunks, one per unit, and 90 at eight).  `least` is the range size that gives
+//   rounds (chunks per range + 4),   rounds = ceil(workgroups / units)
+// is taken.  Where rounds are few, less hides their latencies, and their chunks count more
+// often: a single one 1.25 times (float32, whose chunks are split between
+// barriers, and 64-element rows of 16 bits, whose chunks are half as long, 1.4:
+// one float32 layer of 32768 keys takes 98 us at 16 chunks, one per unit, and 90
+// at eight), two and three of such rows 1.11 and 1.07 times (8 layers x 8
+// segments of 65536 keys: 243 us at k = 2, 236 at 3, 218 at 4).  With 16-bit
+// rows in one set four workgroups share a unit: groups of four rounds follow
+// each other, and a last group that is not full takes nearly a range's time
+// more than its share (128 segments of 81344 keys, d = 128: 1009 us at five
+// rounds, 928 at six, 918 at eight; 256 of 40000: 963 at five and 883 at eight;
+// two sets and float32 show no such steps).  `least` is the range size that gives
 // kSnapTargetGroups workgroups: shorter ranges never pay, and from
 // kSnapMaxRangeChunks on it stands, the chip being full either way.
 // Measured as a score call with `least` and with the rule (32 heads over 8,
 // d = 128, bf16): 1 layer, N = 8192, W = 32: 24.8 -> 23.5 us; N = 32768: 60.7
 // -> 43.6; N = 131072, W = 64: 240 -> 158; 4 layers, N = 20011: 104 -> 88;
 // 8 layers x 2, N = 20011: 285 -> 252 us.
-inline long long snap_range_chunks(long long chunks, long long vsegs, long long least, int elem) {
-    const double alone = elem == 4 ? 1.4 : 1.25;
+inline long long snap_range_chunks(long long chunks, long long vsegs, long long least, bool one_set16,
+                                   bool split, int d) {
+    const bool short_chunks = one_set16 && d == 64;
+    const double few[4] = {1.0, split || short_chunks ? 1.4 : 1.25, short_chunks ? 1.11 : 1.0,
+                           short_chunks ? 1.07 : 1.0};
     if (least >= kSnapMaxRangeChunks) return least;
     long long best = least;
     double cost = -1.0;
@@ -75,7 +86,9 @@ inline long long snap_range_chunks(long long chunks, long long vsegs, long long 
         if (per < least) break;
         if (per > kSnapMaxRangeChunks) continue;
         const long long rounds = (vsegs * ((chunks + per - 1) / per) + kSnapCus - 1) / kSnapCus;
-        const double c = (double)rounds * ((rounds == 1 ? alone : 1.0) * (double)per + 4.0);
+        const double factor = rounds < 4 ? few[rounds] : 1.0;
+        const double tail = one_set16 && rounds > 4 && rounds % 4 != 0 ? 0.8 * (double)per : 0.0;
+        const double c = (double)rounds * (factor * (double)per + 4.0) + tail;
         if (cost < 0.0 || c < cost) {
             cost = c;
             best = per;
@@ -92,7 +105,6 @@ struct SnapPlan {
 
 // elem: bytes per element of the inputs (2 for bf16, 4 for fp32)
 inline SnapPlan snap_plan(int L, int B, int Hq, int Hkv, int N, int W, int d, int elem) {
-    (void)d;
     SnapPlan p{};
     p.segs = L * B * Hkv;
     p.rows = (Hq / Hkv) * W;
@@ -114,7 +126,7 @@ inline SnapPlan snap_plan(int L, int B, int Hq, int Hkv, int N, int W, int d, in
     // the workspace holds the statistics of the smallest ranges: its size does
     // not depend on how the rule below balances them
     const size_t stats_ranges = (size_t)((chunks + per - 1) / per);
-    per = snap_range_chunks(chunks, p.n_vsegs, per, elem);
+    per = snap_range_chunks(chunks, p.n_vsegs, per, elem == 2 && p.sets == 1, elem == 4, d);
     p.range_keys = (int)(per * kSnapChunkKeys);
     p.nranges = (int)((chunks + per - 1) / per);
     // longer ranges leave room for two floats each: the pair keeps the rounding

@@ -310,6 +310,39 @@ def test_topk_slices_fit_the_chip_and_their_records(tmp_path):
         assert s * segs <= max(256, 2 * segs) or s == -(-n // 65504), (segs, n, r, s)
 
 
+SNAP_PLAN_PROGRAM = """
+#include <cstdio>
+#include <cstdlib>
+#include "kve_snap_plan.h"
+int main(int argc, char** argv) {
+    for (int i = 1; i + 7 < argc; i += 8) {
+        int a[8];
+        for (int j = 0; j < 8; ++j) a[j] = atoi(argv[i + j]);
+        const kve::SnapPlan p = kve::snap_plan(a[0], a[1], a[2], a[3], a[4], a[5], a[6], a[7]);
+        printf("%d %d %d\\n", p.n_vsegs * p.nranges, p.range_keys / 64, p.nranges);
+    }
+}
+"""
+
+
+def test_snapkv_ranges_fill_whole_groups_of_workgroups(tmp_path):
+    """Where a score's key ranges make more workgroups than run together (four per
+    compute unit, 16-bit rows in one set), their number is close to a multiple of
+    that; 64-element rows take four per unit rather than fewer, longer ones; a
+    short prompt keeps one or two per unit."""
+    cases = [(8, 2, 8, 8, 81344, 64, 128, 2), (16, 2, 8, 8, 40000, 32, 128, 2), (8, 2, 8, 8, 81344, 32, 64, 2),
+             (8, 1, 8, 8, 65536, 32, 64, 2), (4, 4, 8, 8, 14976, 16, 64, 2), (1, 1, 32, 8, 32768, 32, 128, 2),
+             (1, 1, 32, 8, 8192, 32, 128, 2)]
+    for case, line in zip(cases, _run_plan(tmp_path, SNAP_PLAN_PROGRAM, cases)):
+        groups, per, ranges = (int(x) for x in line.split())
+        assert per * ranges >= -(-case[4] // 64) > per * (ranges - 1), (case, line)
+        rounds = -(-groups // 256)
+        if case[4] > 10000 and (case[0] > 1 or case[6] == 64):
+            assert rounds % 4 == 0, (case, line)
+        else:
+            assert rounds <= 2, (case, line)
+
+
 DECODE_PLAN_PROGRAM = """
 #include <cstdio>
 #include <cstdlib>
