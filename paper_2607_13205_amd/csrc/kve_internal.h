@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "kve_decode_plan.h"
+#include "kve_quest_plan.h"
 #include "kve_snap_plan.h"
 
 namespace kve {
@@ -27,46 +28,6 @@ inline size_t h2o_colsum_offset(int L, int B, int Hq, int N) {
 
 inline size_t h2o_workspace(int L, int B, int Hq, int N) {
     return h2o_colsum_offset(L, B, Hq, N) * sizeof(float) + align_up((size_t)L * B * Hq * N * sizeof(float));
-}
-
-// ---------------------------------------------------------------------------
-// One-shot Quest analogue: a first step writes each head's mean window query
-// (the workspace, [segs, G, d] float32); the page step cuts the prefix of a
-// segment into pages and gives each workgroup a range of whole wave steps of
-// pages: up to kQuestMaxSteps, fewer where that left under kQuestMinGroups
-// workgroups.  A workgroup's start (the mean queries, the first pages' latency)
-// is spread over its steps, and more steps than four only lengthen the tail:
-// 1 layer of 131072 keys (8 KV heads, d = 128, bf16) takes 82 us at one step
-// per workgroup, 55 at two, 50 at four and at eight; 4 x 2 x 24571 keys 79 at
-// two, 71 at four, 73 at eight; 32 x 4 x 32768 keys 1394 at four, 1457 at 16.
-// 1 layer of 8192 keys: 12.8 us at one or two, 15.4 at four (64 workgroups).
-// ---------------------------------------------------------------------------
-constexpr int kQuestMinGroups = 1024;
-constexpr int kQuestMaxSteps = 4;
-constexpr int kQuestMaxGroup = 8;  // query heads per KV head
-constexpr int kQuestMaxPage = 1024;
-
-struct QuestPlan {
-    int segs, G, n_pages, range_pages, nranges;
-    size_t total;
-};
-
-inline QuestPlan quest_plan(int L, int B, int Hq, int Hkv, int N, int W, int d, int elem, int page) {
-    QuestPlan p{};
-    p.segs = L * B * Hkv;
-    p.G = Hq / Hkv;
-    const int P = N - W;
-    p.n_pages = (P + page - 1) / page;
-    const int step = 4 * (64 / (d * elem / 16));  // pages per workgroup step: 4 waves
-    const long long steps = (p.n_pages + step - 1) / step;
-    long long per = steps * p.segs / kQuestMinGroups;
-    const int most = page < 16 ? kQuestMaxSteps * 16 / page : kQuestMaxSteps;  // short pages: as many keys
-    if (per > most) per = most;
-    if (per < 1) per = 1;
-    p.range_pages = (int)(per * step);
-    p.nranges = p.n_pages > 0 ? (int)((p.n_pages + p.range_pages - 1) / p.range_pages) : 1;
-    p.total = align_up((size_t)p.segs * p.G * d * sizeof(float));
-    return p;
 }
 
 // A 4-D view [layer, batch, head, token] of rows of d contiguous elements:

@@ -343,6 +343,38 @@ def test_snapkv_ranges_fill_whole_groups_of_workgroups(tmp_path):
             assert rounds <= 2, (case, line)
 
 
+QUEST_PLAN_PROGRAM = """
+#include <cstdio>
+#include <cstdlib>
+#include "kve_quest_plan.h"
+int main(int argc, char** argv) {
+    for (int i = 1; i + 8 < argc; i += 9) {
+        int a[9];
+        for (int j = 0; j < 9; ++j) a[j] = atoi(argv[i + j]);
+        const kve::QuestPlan p = kve::quest_plan(a[0], a[1], a[2], a[3], a[4], a[5], a[6], a[7], a[8]);
+        printf("%d %d %d\\n", p.n_pages, p.range_pages, p.nranges);
+    }
+}
+"""
+
+
+def test_quest_ranges_weigh_a_workgroups_start(tmp_path):
+    """Ranges cover the pages; four steps of 16-key pages per workgroup with four
+    heads and more per group, two where a start weighs less (float32, fewer
+    heads), one of long pages until 4096 workgroups are full, and at most 32 of
+    short ones."""
+    #        L, B, Hq, Hkv, N, W, d, bytes, page, steps per workgroup
+    cases = [(1, 1, 32, 8, 131072, 32, 128, 2, 16, 4), (4, 2, 32, 8, 24571, 32, 128, 2, 16, 4),
+             (1, 3, 12, 3, 105344, 32, 128, 4, 16, 2), (4, 2, 8, 8, 28834, 64, 128, 2, 16, 2),
+             (4, 1, 32, 8, 32768, 32, 128, 2, 1, 32), (8, 4, 8, 8, 5345, 32, 64, 4, 1, 16),
+             (4, 3, 12, 3, 81792, 16, 128, 2, 64, 1), (8, 1, 32, 8, 32768, 32, 128, 4, 64, 4),
+             (1, 1, 32, 8, 8192, 32, 128, 2, 16, 1)]
+    for case, line in zip(cases, _run_plan(tmp_path, QUEST_PLAN_PROGRAM, [c[:9] for c in cases])):
+        pages, per, ranges = (int(x) for x in line.split())
+        assert per * ranges >= pages > per * (ranges - 1), (case, line)
+        assert per == case[9] * 4 * (64 // (case[6] * case[7] // 16)), (case, line)
+
+
 DECODE_PLAN_PROGRAM = """
 #include <cstdio>
 #include <cstdlib>
