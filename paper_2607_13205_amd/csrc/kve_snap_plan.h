@@ -14,8 +14,9 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 // of 256 for bf16 when the window has more than 128 rows: a wave then holds
 // two sets of 32 rows, so that K is read once per pass for up to 256 rows.  Each
 // vseg's keys are split into ranges of whole 64-key chunks, one workgroup each;
-// pass 1 writes one log-sum-exp per (vseg, range, row), a combine step reduces
-// them to one per row, pass 2 writes the column sums of each row group (a
+// pass 1 writes the statistics of each (vseg, range, row), a {reference, sum}
+// pair or one log-sum-exp; a combine step, or pass 2 itself, reduces them to one
+// log-sum-exp per row; pass 2 writes the column sums of each row group (a
 // plane), and the pool step adds the planes and max-pools the prefix.
 // ---------------------------------------------------------------------------
 constexpr int kSnapRowsPerGroup = 128;

@@ -19,10 +19,12 @@
 //
 //   pass 1   snap_pass1    S^T = K Q^T: each lane holds one row and 16 keys per
 //                          32-key block, so the running row sum of
-//                          exp2(x - ref) stays in the lane; one log-sum-exp per
-//                          (vseg, range, row) is written.
+//                          exp2(x - ref) stays in the lane; per (vseg, range,
+//                          row) a {ref, sum} pair is written, or one
+//                          log-sum-exp where the workspace has no room for two.
 //   combine  snap_combine  per row: lse2 over the ranges (+inf for padding rows);
-//                          pass 2 does it itself up to kMergeRanges ranges.
+//                          pass 2 does it itself, before its keys (float32: while
+//                          its first chunk loads), up to kMergeRanges ranges.
 //   pass 2   snap_pass2    S = Q K^T: each lane holds one key and 16 rows per
 //                          block, so the column sum of exp2(x - lse2) is a lane
 //                          sum plus one shuffle; the four row blocks (waves)
