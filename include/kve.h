@@ -212,6 +212,7 @@ size_t kve_h2o_workspace_size(int L, int B, int Hq, int Hkv, int N, int d);
  *
  * Two passes on the matrix cores: per-row log-sum-exp over the causal row,
  * then column sums per query head, added over the G heads in head order.
+ * Float32 rows are multiplied as in kve_snapkv_score.
  * Requires Hq/Hkv <= 128.  The workspace (kve_h2o_workspace_size bytes,
  * 256-byte aligned, owned by the caller) holds, per (layer, sample, query
  * head), one start value per query row (rows padded to a multiple of 64

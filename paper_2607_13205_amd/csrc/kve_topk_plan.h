@@ -27,9 +27,12 @@ inline bool topk_in_regs(size_t segs, int N, int R) {
 }
 
 // Segments split into slices, one workgroup each (topk_count, topk_stage), up to
-// kSplitSegs segments: 64 x 65536 keys take 48 us split and 60 whole, 64 x
-// 131072 73 and 94; 256 x 65536 127 and 73 (the slices' workgroups of 16 waves,
-// one per compute unit, then queue for the chip).
+// kSplitSegs segments, where each still has four slices: 64 x 65536 keys take
+// 48 us split and 60 whole, 64 x 131072 73 and 94.  In three or two slices the
+// two further kernels take back what they give (one bucket, split and whole: 72
+// x 20000 keys 30 and 27 us, x 131072 80 and 90; 96 x 65536 52 and 55, x 131072
+// 104 and 91; 128 x 65536 54 and 55; 160, two queueing rounds, 71 and 56; 255
+// 80 and 71).
 constexpr size_t kSplitSegs = 64;
 constexpr int kMaxSlices = 64;
 // Workgroups of all segments up to one per compute unit, slices of at least
