@@ -380,8 +380,8 @@ DECODE_PLAN_PROGRAM = """
 #include <cstdlib>
 #include "kve_decode_plan.h"
 int main(int argc, char** argv) {
-    for (int i = 1; i + 1 < argc; i += 2) {
-        const kve::DecodePlan p = kve::decode_plan(1, atoi(argv[i]), 4, 1, atoi(argv[i + 1]), 128);
+    for (int i = 1; i + 2 < argc; i += 3) {
+        const kve::DecodePlan p = kve::decode_plan(1, atoi(argv[i]), 4, 1, atoi(argv[i + 1]), atoi(argv[i + 2]));
         printf("%d %d %zu\\n", p.nsplit, p.split_keys / kve::kDecodeQuantum, p.off_ml);
     }
 }
@@ -389,22 +389,30 @@ int main(int argc, char** argv) {
 
 
 def test_decode_splits_fill_the_compute_units(tmp_path):
-    """Splits cover the cache and fit the workspace; unless they are already as
-    short as three workgroups per compute unit make them, none is longer than 16
-    quanta (the counts of a batch differ) and the rounds of one workgroup per
-    unit are at least 0.85 full."""
-    cases = [(s, k) for s in (1, 2, 7, 8, 31, 32, 64, 100, 128, 136, 160, 200, 248, 255, 256, 257, 264, 288, 320, 384,
-                              448, 504, 512, 513, 640, 800, 1016, 1023, 1024, 1025, 5000)
-             for k in (1, 127, 128, 129, 1639, 2048, 2049, 6000, 20000, 32768, 200001)]
-    for (segs, k_cap), line in zip(cases, _run_plan(tmp_path, DECODE_PLAN_PROGRAM, cases)):
+    """Splits cover the cache and fit the workspace.  Short ones stay one
+    workgroup per compute unit; of the others, unless they are already as short
+    as three workgroups per unit make them, none is longer than 16 quanta (the
+    counts of a batch differ) and the rounds of one workgroup per unit are at
+    least 0.85 full."""
+    cases = [(s, k, d) for s in (1, 2, 7, 8, 31, 32, 64, 96, 100, 128, 136, 160, 200, 248, 255, 256, 257, 264, 288, 320,
+                                 384, 448, 504, 512, 513, 640, 800, 1016, 1023, 1024, 1025, 5000)
+             for k in (1, 127, 128, 129, 400, 820, 1639, 2048, 2049, 3277, 6000, 20000, 32768, 200001)
+             for d in (64, 128)]
+    for (segs, k_cap, d), line in zip(cases, _run_plan(tmp_path, DECODE_PLAN_PROGRAM, cases)):
         ns, per, room = (int(x) for x in line.split())
         quanta = -(-k_cap // 128)
-        assert ns * per >= quanta > (ns - 1) * per, (segs, k_cap, line)
-        assert segs * ns * 4 * 128 * 4 <= room, (segs, k_cap, line)
+        assert ns * per >= quanta > (ns - 1) * per, (segs, k_cap, d, line)
+        assert segs * ns * 4 * d * 4 <= room, (segs, k_cap, d, line)
+        one = -(-quanta // min(quanta, -(-256 // segs)))  # quanta per split at one workgroup per unit
+        whole = one >= quanta
+        if one <= (7 if whole else 4) * (128 // d):
+            assert per == one, (segs, k_cap, d, line)
+            continue
         rounds = -(-segs * ns // 256)
         even = rounds == 1 or segs * ns >= 0.85 * 256 * rounds
-        least_of_three = -(-quanta // min(quanta, -(-768 // segs)))  # quanta per split at three workgroups per unit
-        assert (per <= 16 and even) or per <= least_of_three, (segs, k_cap, line)
+        longest = 16 * (128 // d) if ns == 1 else 16
+        least_of_three = -(-quanta // min(quanta, -(-768 // segs)))  # at three workgroups per unit
+        assert (per <= longest and even) or per <= least_of_three, (segs, k_cap, d, line)
 
 
 @pytest.mark.parametrize("L,B,Hq,Hkv,N,W,d", [(1, 1, 2, 1, 512, 16, 64), (1, 1, 32, 8, 8192, 32, 128),
